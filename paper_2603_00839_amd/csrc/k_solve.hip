@@ -5,12 +5,13 @@
 // The Arnoldi steps already reduced H (the (k+1) x k Hessenberg matrix) by
 // Givens rotations to H = Q [R; 0] with Q^T beta e1 = [g_R; gamma], so
 //   ||beta e1 - H y||^2 + mu ||y||^2 = ||g_R - R y||^2 + gamma^2 + mu ||y||^2.
-// With the SVD R = U diag(s) W^T (one-sided Jacobi: plane rotations of the
-// columns of R accumulated in W, in LDS) and ghat = U^T g_R,
+// With the SVD R = U diag(s) W^T (one-sided Jacobi, in LDS: plane rotations of
+// the columns of R^T until they are orthogonal; rotated along with them, the
+// entries of g_R become ghat = U^T g_R, and column i ends as s_i w_i) and ghat,
 //   phi(mu) = sum_i (mu / (s_i^2 + mu))^2 ghat_i^2 + gamma^2
 // is the projected residual; it increases from gamma^2 to beta^2 and the
 // discrepancy principle takes the root of phi(mu) = (eta delta)^2, found by
-// multisection (64 points per pass) in log(mu).  Then y = W diag(s / (s^2 + mu)) ghat, the filter
+// multisection in log(mu).  Then y = W diag(s / (s^2 + mu)) ghat, the filter
 // form of the stacked least-squares problem (13).  With the GCV rule (Sec. 3,
 // parameter selection via GCV) mu minimises
 //   GCV(mu) = phi(mu) / (1 + sum_i mu / (s_i^2 + mu))^2
@@ -24,8 +25,28 @@ namespace rtg {
 
 // A pair of columns counts as orthogonal once |a_p . a_q| <= tol ||a_p|| ||a_q||;
 // below about n * eps the inner product is rounding noise and rotations stop
-// making progress.
-constexpr double JACOBI_TOL = 1e-13;
+// making progress.  A sweep that met no cosine above JACOBI_LAST ends the
+// process without another one to confirm it: convergence is quadratic, and
+// with the single-precision angle used here a rotation leaves at most 1e-7 of
+// the cosine it met, so the largest one left is below tol.
+constexpr double JACOBI_TOL2 = 1e-26;    // (1e-13)^2
+constexpr double JACOBI_LAST2 = 1e-15;   // (3e-8)^2
+
+// Sum over a group of 8 lanes, in every lane (VALU cross-lane moves, no LDS
+// round trip): neighbours, then pairs within a quad, then the mirrored quad.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double sum8(double v) {
+    v += dpp_f64<0xB1>(v);     // quad_perm [1, 0, 3, 2]
+    v += dpp_f64<0x4E>(v);     // quad_perm [2, 3, 0, 1]
+    v += dpp_f64<0x141>(v);    // row_half_mirror
+    return v;
+}
 
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
@@ -44,19 +65,36 @@ __device__ __forceinline__ double proj_res2(const double* sig, const double* gh,
     return wave_sum(s) + gp2;
 }
 
-__global__ void __launch_bounds__(1024) k_solve(const Desc* __restrict__ descs) {
-    constexpr int LD = MMAX + 1;
-    __shared__ double As[MMAX * LD];
-    __shared__ double Ws[MMAX * LD];
-    __shared__ double gR[MMAX], sig[MMAX], gh[MMAX], fco[MMAX];
-    __shared__ int s_rot;
+// A chain of (sweeps) x (k - 1) rounds, each a barrier: the length of a round
+// is what the kernel takes.  The rotations work on R^T with g_R as one more
+// row, so no matrix W is accumulated (half the LDS traffic of a round); the
+// dot products are reduced by cross-lane moves instead of through LDS; the
+// rotation's angle is taken in single precision (it only steers convergence:
+// cosine and sine are normalised in float64, so the rotations are orthogonal
+// to rounding).  Eight lanes per pair: a problem of k = 50 then has one wave
+// per SIMD.  With sixteen it had two, and a round was bound by their float64
+// issue (1,750 clocks against 1,520).  NR: rows per lane, k <= 8 NR (a runtime
+// row count cost a scalar branch per row).  One problem, k = 50: 920 -> 350 us;
+// k = 20: 176 -> 75 us.
+template <int NR>
+__global__ void __launch_bounds__(384) k_solve(const Desc* __restrict__ descs) {
+    // A lane holds the row pairs 2 gl, 2 gl + 1 (mod 16): 16-byte LDS accesses.
+    // Column stride in doubles: 16 mod 32, so that two neighbouring groups,
+    // which read neighbouring columns, meet different banks.
+    constexpr int LD = (NR <= 2) ? 16 : (NR <= 6 ? 48 : (NR <= 10 ? 80 : 112));
+    static_assert(LD >= 8 * NR && NR % 2 == 0 && NR <= 14, "column stride");
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(16))) double As[8 * NR * LD];
+    __shared__ double sig[MMAX], gh[MMAX], fco[MMAX];
+    __shared__ int s_big[3];                      // per sweep: a cosine above JACOBI_LAST was met
+    __shared__ int s_cnt[2][8];                  // per wave: its points below the target (two passes in turn)
     __shared__ double s_mu;
     __shared__ int s_flags;
 
     const Desc& d = descs[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nwave = blockDim.x >> 6;
-    const int k = d.state[ST_MEFF];
+    const int k = uniform_int(d.state[ST_MEFF]);
     const int m = d.m;
     const double beta = d.scal[SC_BETA];
     const double* gvec = d.gv + 2 * m;
@@ -77,89 +115,106 @@ __global__ void __launch_bounds__(1024) k_solve(const Desc* __restrict__ descs) 
         }
         return;
     }
-    // ---- load R (upper triangular, column-major, leading dimension m) and W = I
-    for (int e = tid; e < k * k; e += blockDim.x) {
-        const int c = e / k, r = e % k;
-        As[c * LD + r] = (r <= c) ? d.R[(size_t)c * m + r] : 0.0;
-        Ws[c * LD + r] = (r == c) ? 1.0 : 0.0;
-    }
-    if (tid < k) gR[tid] = gvec[tid];
+    // ---- load R^T: column c of As is row c of R (upper triangular, stored
+    // column-major with leading dimension m), rows padded with zeros to 8 NR
+    for (int r = wave; r < 8 * NR; r += nwave)
+        for (int c = lane; c < k; c += 64)
+            As[c * LD + r] = (r < k && c <= r) ? *gptr(d.R + (size_t)r * m + c) : 0.0;
+    if (tid < k) gh[tid] = gvec[tid];
+    if (tid < 3) s_big[tid] = 0;
     const double gam = fabs(gvec[k]);
     __syncthreads();
 
     // ---- one-sided Jacobi, round-robin (circle) ordering of column pairs.
-    // Sixteen lanes handle one pair (k <= 96: at most six rows per lane), so
-    // all pairs of a round (k/2 <= 48 <= 64 groups) rotate concurrently.
+    // Eight lanes handle one pair, and there is a group for every pair of a round.
     const int nb = k + (k & 1);
-    const int grp = tid >> 4, gl = tid & 15, ngrp = blockDim.x >> 4;
+    const int grp = tid >> 3, gl = tid & 7;
+    // this group's pair of round 0 (position 0 stays, the others step round the circle)
+    int qa = grp - 1, qb = nb - 2 - grp;
     for (int sweep = 0; sweep < 60; ++sweep) {
-        if (tid == 0) s_rot = 0;
-        __syncthreads();
+        const int slot = sweep % 3;
+        bool big = false;
+        int oa = qa, ob = qb;                     // (position - 1 + round) mod (nb - 1)
         for (int rd = 0; rd < nb - 1; ++rd) {
-            for (int pi = grp; pi < nb / 2; pi += ngrp) {
-                const int pos_b = nb - 1 - pi;
-                const int pa = pi == 0 ? 0 : 1 + (pi - 1 + rd) % (nb - 1);
-                const int pb = 1 + (pos_b - 1 + rd) % (nb - 1);
-                if (pa >= k || pb >= k) continue;      // uniform within the 16-lane group
-                double* ca = As + pa * LD;
-                double* cb = As + pb * LD;
-                double al = 0.0, be = 0.0, ga = 0.0;
-                for (int r = gl; r < k; r += 16) {
-                    const double x = ca[r], y = cb[r];
-                    al += x * x; be += y * y; ga += x * y;
-                }
+            const int pa = grp == 0 ? 0 : 1 + oa, pb = 1 + ob;
+            oa = (oa + 1 >= nb - 1) ? 0 : oa + 1;
+            ob = (ob + 1 >= nb - 1) ? 0 : ob + 1;
+            if (grp < nb / 2 && pa < k && pb < k) {   // uniform within the group
+                d2* ca = (d2*)(As + pa * LD + 2 * gl);
+                d2* cb = (d2*)(As + pb * LD + 2 * gl);
+                double x[NR], y[NR];
 #pragma unroll
-                for (int off = 8; off > 0; off >>= 1) {
-                    al += __shfl_xor(al, off, 16);
-                    be += __shfl_xor(be, off, 16);
-                    ga += __shfl_xor(ga, off, 16);
+                for (int q = 0; q < NR; q += 2) {
+                    const d2 u = ca[4 * q], v = cb[4 * q];
+                    x[q] = u[0]; x[q + 1] = u[1];
+                    y[q] = v[0]; y[q + 1] = v[1];
                 }
-                if (ga != 0.0 && fabs(ga) > JACOBI_TOL * sqrt(al * be)) {
-                    const double zeta = (be - al) / (2.0 * ga);
-                    const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    const double cth = 1.0 / sqrt(1.0 + t * t), sth = cth * t;
-                    double* wa = Ws + pa * LD;
-                    double* wb = Ws + pb * LD;
-                    for (int r = gl; r < k; r += 16) {
-                        const double x = ca[r], y = cb[r];
-                        ca[r] = cth * x - sth * y;
-                        cb[r] = sth * x + cth * y;
-                        const double u = wa[r], v = wb[r];
-                        wa[r] = cth * u - sth * v;
-                        wb[r] = sth * u + cth * v;
+                const double ga0 = gh[pa], gb0 = gh[pb];
+                double al = x[0] * x[0], be = y[0] * y[0], ga = x[0] * y[0];
+#pragma unroll
+                for (int q = 1; q < NR; ++q) {
+                    al = fma(x[q], x[q], al);
+                    be = fma(y[q], y[q], be);
+                    ga = fma(x[q], y[q], ga);
+                }
+                al = sum8(al);
+                be = sum8(be);
+                ga = sum8(ga);
+                const double g2 = ga * ga, ab = al * be;
+                if (g2 > JACOBI_TOL2 * ab) {
+                    big = big || g2 > JACOBI_LAST2 * ab;
+                    // t = tan of the angle: sign(z) / (|z| + sqrt(1 + z^2)), z = (be - al) / (2 ga)
+                    const double df = be - al, g2x = 2.0 * ga;
+                    // (both scaled to about 1 first, so that their single-precision
+                    // values do not overflow or vanish together)
+                    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(df), fabs(g2x)));
+                    const float dff = (float)__builtin_ldexp(df, ex), gf = (float)__builtin_ldexp(g2x, ex);
+                    const float rt = __builtin_amdgcn_sqrtf(fmaf(dff, dff, gf * gf));
+                    const float tf = gf * __builtin_amdgcn_rcpf(fabsf(dff) + rt);
+                    const double t = (double)(dff < 0.f ? -tf : tf);
+                    const double q1 = fma(t, t, 1.0);
+                    // 1 / sqrt(q1), 1 <= q1 <= 2: the hardware's estimate and two Newton steps
+                    double cth = __builtin_amdgcn_rsq(q1);
+                    cth = fma(cth * 0.5, fma(-q1 * cth, cth, 1.0), cth);
+                    cth = fma(cth * 0.5, fma(-q1 * cth, cth, 1.0), cth);
+                    const double sth = cth * t;
+#pragma unroll
+                    for (int q = 0; q < NR; q += 2) {
+                        ca[4 * q] = d2{fma(cth, x[q], -sth * y[q]), fma(cth, x[q + 1], -sth * y[q + 1])};
+                        cb[4 * q] = d2{fma(sth, x[q], cth * y[q]), fma(sth, x[q + 1], cth * y[q + 1])};
                     }
-                    if (gl == 0) s_rot = 1;
+                    if (gl == 0) {
+                        gh[pa] = fma(cth, ga0, -sth * gb0);
+                        gh[pb] = fma(sth, ga0, cth * gb0);
+                    }
                 }
+            }
+            if (rd == nb - 2) {
+                if (big && gl == 0) s_big[slot] = 1;
+                if (tid == 0) s_big[(sweep + 1) % 3] = 0;   // last read two sweeps ago
             }
             __syncthreads();
         }
-        const int rot = s_rot;
-        __syncthreads();
-        if (!rot) break;
+        if (!s_big[slot]) break;
     }
-    // ---- singular values and ghat = U^T g_R
-    for (int i = wave; i < k; i += nwave) {
-        double nn = 0.0, gg = 0.0;
-        for (int r = lane; r < k; r += 64) {
-            const double x = As[i * LD + r];
-            nn += x * x;
-            gg += x * gR[r];
+    // ---- singular values: the norms of the columns (ghat is in gh)
+    for (int i = grp; i < k; i += blockDim.x >> 3) {
+        double nn = 0.0;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+            const double x = As[i * LD + gl + 8 * q];
+            nn = fma(x, x, nn);
         }
-        nn = wave_sum(nn);
-        gg = wave_sum(gg);
-        if (lane == 0) {
-            const double s = sqrt(nn);
-            sig[i] = s;
-            gh[i] = s > 0.0 ? gg / s : 0.0;
-        }
+        nn = sum8(nn);
+        if (gl == 0) sig[i] = sqrt(nn);
     }
     __syncthreads();
-    // ---- mu: fixed, or the discrepancy principle (wave 0)
-    if (wave == 0) {
-        const double gp2 = gam * gam;
+    // ---- mu: fixed, by GCV (wave 0), or by the discrepancy principle (every wave)
+    const double gp2 = gam * gam;
+    if (d.mu_fixed || d.mu_rule == RTG_MU_GCV) {
+      if (wave == 0) {
         double mu = d.mu;
-        int flags = 0;
-        if (!d.mu_fixed && d.mu_rule == RTG_MU_GCV) {
+        if (!d.mu_fixed) {
             // GCV at log(mu) = x, and the (value, position) minimum over the wave
             auto gcv_at = [&](double x) {
                 const double mu_l = exp(x);
@@ -227,48 +282,81 @@ __global__ void __launch_bounds__(1024) k_solve(const Desc* __restrict__ descs) 
                 if (!(hi - lo > 1e-12)) break;
             }
             mu = exp(xbest);
-        } else if (!d.mu_fixed) {
-            const double t = d.eta * d.delta;
-            const double t2 = t * t;
-            if (t2 <= gp2) {
-                mu = 0.0;
-                flags |= RTG_F_DISCREP_UNREACHABLE;
-            } else if (t2 >= beta * beta) {
-                mu = INFINITY;
-                flags |= RTG_F_MU_INF;
-            } else {
-                double smax = 0.0;
-                for (int i = lane; i < k; i += 64) smax = fmax(smax, sig[i]);
-                smax = wave_max(smax);
-                const double smax2 = smax > 0.0 ? smax * smax : 1.0;
-                double lo = log(smax2) - 80.0, hi = log(smax2) + 80.0;
-                for (int it = 0; it < 40 && proj_res2(sig, gh, k, exp(lo), gp2, lane) > t2; ++it) lo -= 40.0;
-                for (int it = 0; it < 40 && proj_res2(sig, gh, k, exp(hi), gp2, lane) < t2; ++it) hi += 40.0;
-                // Multisection in log(mu): each lane evaluates phi at one of 64
-                // interior points of [lo, hi]; phi increases with mu, so the
-                // lanes below the target form a prefix and the bracket shrinks
-                // 65-fold per pass (the bracket bisection would reach, six
-                // halvings at a time), until it stops shrinking.
-                for (int it = 0; it < 16; ++it) {
-                    const double x = lo + (hi - lo) * (double)(lane + 1) / 65.0;
-                    double ph = gp2;
-                    const double mu_l = exp(x);
-                    for (int i = 0; i < k; ++i) {
-                        const double f = mu_l / (sig[i] * sig[i] + mu_l);
-                        ph += f * f * gh[i] * gh[i];
-                    }
-                    const unsigned long long below = __ballot(ph < t2);
-                    const int pfx = (below == ~0ull) ? 64 : __builtin_ctzll(~below);
-                    const double nlo = pfx > 0 ? __shfl(x, pfx - 1, 64) : lo;
-                    const double nhi = pfx < 64 ? __shfl(x, pfx, 64) : hi;
-                    if (!(nhi - nlo < hi - lo)) break;
-                    lo = nlo;
-                    hi = nhi;
-                }
-                mu = exp(0.5 * (lo + hi));
-            }
         }
         if (lane == 0) {
+            s_mu = mu;
+            s_flags = 0;
+        }
+      }
+    } else {
+        const double t = d.eta * d.delta;
+        const double t2 = t * t;
+        double mu;
+        int flags = 0;
+        if (t2 <= gp2) {
+            mu = 0.0;
+            flags = RTG_F_DISCREP_UNREACHABLE;
+        } else if (t2 >= beta * beta) {
+            mu = INFINITY;
+            flags = RTG_F_MU_INF;
+        } else {
+            double smax = 0.0;
+            for (int i = lane; i < k; i += 64) smax = fmax(smax, sig[i]);
+            smax = wave_max(smax);
+            const double smax2 = smax > 0.0 ? smax * smax : 1.0;
+            double lo = log(smax2) - 80.0, hi = log(smax2) + 80.0;
+            for (int it = 0; it < 40 && proj_res2(sig, gh, k, exp(lo), gp2, lane) > t2; ++it) lo -= 40.0;
+            for (int it = 0; it < 40 && proj_res2(sig, gh, k, exp(hi), gp2, lane) < t2; ++it) hi += 40.0;
+            // Multisection: every 8-lane group evaluates phi at its interior
+            // point of the bracket; phi increases with mu, so the points below
+            // the target form a prefix, and with P groups the bracket shrinks
+            // P + 1-fold per pass, until it stops shrinking.  In log(mu) while
+            // the bracket is wider than a tenth, then in mu itself (a float64
+            // exponential is half of a pass).  All waves hold the same
+            // bracket: the next one follows from the number of points below.
+            const int P = blockDim.x >> 3;
+            const double iP = 1.0 / (double)(P + 1), frac = (double)(grp + 1) * iP;
+            double sq[NR], gq[NR];
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                const int i = gl + 8 * q;
+                sq[q] = i < k ? sig[i] * sig[i] : 1.0;
+                gq[q] = i < k ? gh[i] : 0.0;
+            }
+            bool in_log = true;
+            for (int it = 0; it < 40; ++it) {
+                if (in_log && hi - lo < 0.1) {
+                    in_log = false;
+                    lo = exp(lo);
+                    hi = exp(hi);
+                }
+                const double x = lo + (hi - lo) * frac;
+                const double mu_l = in_log ? exp(x) : x;
+                double ph = 0.0;
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    const double f = mu_l / (sq[q] + mu_l) * gq[q];
+                    ph = fma(f, f, ph);
+                }
+                ph = sum8(ph) + gp2;
+                const unsigned long long below = __ballot(ph < t2);
+                if (lane == 0) s_cnt[it & 1][wave] = ((below == ~0ull) ? 64 : __builtin_ctzll(~below)) >> 3;
+                __syncthreads();
+                int pfx = 0;
+                for (int w = 0; w < nwave; ++w) {
+                    const int c = s_cnt[it & 1][w];
+                    pfx += c;
+                    if (c < 8) break;
+                }
+                const double nlo = pfx > 0 ? lo + (hi - lo) * ((double)pfx * iP) : lo;
+                const double nhi = pfx < P ? lo + (hi - lo) * ((double)(pfx + 1) * iP) : hi;
+                if (!(nhi - nlo < hi - lo)) break;
+                lo = nlo;
+                hi = nhi;
+            }
+            mu = in_log ? exp(0.5 * (lo + hi)) : 0.5 * (lo + hi);
+        }
+        if (tid == 0) {
             s_mu = mu;
             s_flags = flags;
         }
@@ -277,14 +365,16 @@ __global__ void __launch_bounds__(1024) k_solve(const Desc* __restrict__ descs) 
     const double mu = s_mu;
     if (tid < k) {
         const double s = sig[tid];
-        fco[tid] = isinf(mu) ? 0.0 : (s > 0.0 ? s / (s * s + mu) * gh[tid] : 0.0);
+        // y = sum_i (s_i / (s_i^2 + mu)) ghat_i w_i, and column i holds s_i w_i
+        fco[tid] = isinf(mu) ? 0.0 : (s > 0.0 ? s / (s * s + mu) * gh[tid] / s : 0.0);
     }
     __syncthreads();
-    // ---- y = W f; coefficients of X = X0 + sum_j y_j V_j
+    // ---- y; coefficients of X = X0 + sum_j y_j V_j
     bool ok = true;
     if (tid < k) {
         double yv = 0.0;
-        for (int i = 0; i < k; ++i) yv += Ws[i * LD + tid] * fco[i];
+#pragma unroll 8
+        for (int i = 0; i < k; ++i) yv += As[i * LD + tid] * fco[i];
         d.y[tid] = yv;
         // (a V_1 stored unnormalised carries its 1 / beta in its coefficient)
         d.coef[tid] = (float)(-yv * ((d.lazy_v1 && tid == 0) ? 1.0 / beta : 1.0));
@@ -292,7 +382,6 @@ __global__ void __launch_bounds__(1024) k_solve(const Desc* __restrict__ descs) 
     }
     const int allok = __syncthreads_and(ok ? 1 : 0);
     if (wave == 0) {
-        const double gp2 = gam * gam;
         const double rp2 = isinf(mu) ? beta * beta : proj_res2(sig, gh, k, mu, gp2, lane);
         if (lane == 0) {
             int flags = d.state[ST_FLAGS] | s_flags;
@@ -431,13 +520,17 @@ __global__ void k_finish_arnoldi(const Desc* __restrict__ descs, double* H, doub
 }
 
 hipError_t launch_solve(const Desc* d, int count, int mmax, hipStream_t s) {
-    // sixteen lanes per Jacobi column pair; at least 128 threads (one per
-    // column for the final products), so that small problems synchronise
-    // few waves
-    int threads = 16 * ((mmax + 1) / 2);
-    threads = (threads + 63) / 64 * 64;
-    threads = threads < 128 ? 128 : (threads > 1024 ? 1024 : threads);
-    hipLaunchKernelGGL(k_solve, dim3(count), dim3(threads), 0, s, d);
+    // eight lanes per Jacobi column pair, and a group for each point of the
+    // multisection: a wave per SIMD at least (mmax <= 96: at most 384 threads)
+    int threads = 8 * ((mmax + 1) / 2);
+    threads = threads < 256 ? 256 : (threads + 63) / 64 * 64;
+#define RTG_SOLVE(NRV) hipLaunchKernelGGL(k_solve<NRV>, dim3(count), dim3(threads), 0, s, d)
+    if (mmax <= 16) RTG_SOLVE(2);
+    else if (mmax <= 32) RTG_SOLVE(4);
+    else if (mmax <= 64) RTG_SOLVE(8);
+    else if (mmax <= 80) RTG_SOLVE(10);
+    else RTG_SOLVE(12);
+#undef RTG_SOLVE
     return hipGetLastError();
 }
 
