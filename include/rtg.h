@@ -333,9 +333,10 @@ int rtg_solve_batched_fallback_end(int count, const rtg_problem* probs,
  *                 the stacked sketch rows fit, else 4) or 4
  *   step_rows     fused bfloat16 Arnoldi step: the same, 2 or 4
  *   step_toeplitz fused step: 1 Toeplitz taps (all bands Toeplitz), 0 band rows
- *   gram_pairs    sketched inner products: (a, b) sketch pairs per workgroup,
- *                 256, 512 or 1024 (capped at 4096 / l3 finished values; never
- *                 below the library's own choice for the problem)
+ *   gram_pairs    sketched inner products: (a, b) sketch pairs per workgroup:
+ *                 256 (the library's own choice for the batch: 256, or fewer
+ *                 where the batch or the problem's shape asks for it), 512 or
+ *                 1024 (capped at 4096 / l3 finished values)
  *   persist       1: the Arnoldi process of the whole batch (the start and
  *                 every step of every problem) as one persistent launch whose
  *                 workgroups take the stages' tiles in order from a device-side

@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
             } else {
                 const Task k = decode(a, x, t);
                 const int* starts = a.starts[k.kind];
-                const int p = find_problem(starts, a.count, k.b);
+                const int p = find_problem_1(starts, a.count, k.b);
                 const Desc& d = descs[p];
 #pragma unroll
                 for (int q = 0; q < NKIND; ++q) {
@@ -266,7 +266,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
         __syncthreads();
         if (tid == 0) {
-            int* ctr = descs[find_problem(starts, a.count, k.b)].state + ST_DONE + k.kind;
+            int* ctr = descs[find_problem_1(starts, a.count, k.b)].state + ST_DONE + k.kind;
             Pending& pd = s_pend;
             int i = 0;
             while (i < pd.used && pd.ctr[i] != ctr) ++i;

@@ -104,9 +104,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     float* Ys = (float*)su;                             // mode-1 results (after the last block)
 
     const int b = xcd_tile(blockIdx.x, gridDim.x);
-    const int p = find_problem(starts, count, b);
-    const Desc& d = descs[p];
-    const int tile = uniform_int(b - starts[p]);
+    const TileOf at = find_problem(starts, count, b);
+    const Desc& d = descs[at.p];
+    const int tile = at.tile;
     if (d.state[ST_ACTIVE] == 0) return;
 
     const int tid = threadIdx.x, lane = tid & 63;

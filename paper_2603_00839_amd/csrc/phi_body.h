@@ -397,8 +397,8 @@ __device__ __forceinline__ void phi_tile(const PhiArgs& a, int tile, float* smem
 template <int R, bool BF16IN, int JT, bool ST, int SL, bool TP>
 __device__ __forceinline__ void phi_batched_task(const Desc* __restrict__ descs, const int* __restrict__ starts,
                                                  int count, int src_sel, int src_index, int b, float* smem) {
-    const int p = find_problem(starts, count, b);
-    const Desc& d = descs[p];
+    const TileOf at = find_problem(starts, count, b);
+    const Desc& d = descs[at.p];
     if (src_sel == PS_BASIS && d.state[ST_ACTIVE] == 0) return;
     PhiArgs a;
     a.I1 = d.I1; a.I2 = d.I2; a.J = d.J; a.r1 = d.r1; a.r2 = d.r2; a.rB = d.rB;
@@ -416,7 +416,7 @@ __device__ __forceinline__ void phi_batched_task(const Desc* __restrict__ descs,
     }
     a.dst = d.W;
     a.dst_bf = (src_sel == PS_X0_V1) ? (bf16_t*)d.V : nullptr;
-    phi_tile<R, BF16IN, JT, ST, SL, TP>(a, uniform_int(b - starts[p]), smem);
+    phi_tile<R, BF16IN, JT, ST, SL, TP>(a, at.tile, smem);
 }
 
 }  // namespace rtg

@@ -90,7 +90,10 @@ Layout problem_layout(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16) {
     L.PW = take(part);
     L.PV = take(part);
     L.SV = take(sk_bufs ? (size_t)(m + 1) * Ls * sizeof(float) : 0);
-    L.dots = take((size_t)L.ntile_gram * (MMAX + 2) * 2 * sizeof(double));
+    // (shares of every workgroup, at the smallest chunk that a plan may take)
+    const int chs = gram_pairs_small(sk->l3, op->J, L.n_i2t);
+    const int gram_max = sk->identity ? L.ntile_gram : (sk->l1 * sk->l2 + chs - 1) / chs;
+    L.dots = take((size_t)gram_max * (MMAX + 2) * 2 * sizeof(double));
     L.G = take((size_t)(m + 1) * (m + 1) * sizeof(double));
     L.H = take((size_t)(m + 1) * m * sizeof(double));
     L.R = take((size_t)m * m * sizeof(double));
@@ -332,14 +335,27 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
     plan.phi_jt = (tune && (tune->phi_jt == 4 || tune->phi_jt == 8)) ? tune->phi_jt : phi_jt(maxJ);
     for (auto& d : descs)
         if (d.ntile[KIND_PHI] > 0) d.ntile[KIND_PHI] = phi_tiles(d.I1, d.I2, d.J, plan.phi_jt);
-    // sketched-Gram chunks: at least the default (the dots area of the
-    // workspace holds the default's workgroup count), at most 4096 finished
-    // values per workgroup
+    // sketched-Gram chunks.  A chosen gram_pairs above the base of 256: that
+    // many, at most 4096 finished values per workgroup.  Otherwise 256, or 64
+    // where the batch then still has at most GRAM_SMALL_WGS workgroups: a
+    // workgroup is a chain of latencies whose middle part goes with its pairs,
+    // and a few hundred workgroups run side by side.  (One 512x512x3 problem:
+    // 16 workgroups of 256 pairs or 64 of 64.)
+    constexpr long long GRAM_SMALL_WGS = 1024;
+    long long small_wgs = 0;
+    for (auto& d : descs)
+        if (!d.unsketched) {
+            const int ch = gram_pairs_small(d.l3, d.J, d.n_i2t);
+            small_wgs += (d.l1 * d.l2 + ch - 1) / ch;
+        }
+    const bool small = small_wgs <= GRAM_SMALL_WGS * nsides;
     for (auto& d : descs) {
         d.gram_ch = 0;
-        if (!tune || tune->gram_pairs <= 0 || d.unsketched || gram_split(d.l3, d.J, d.n_i2t)) continue;
+        if (d.unsketched || gram_split(d.l3, d.J, d.n_i2t)) continue;
         const int def = gram_pairs_per_block(d.l3, d.J, d.n_i2t);
-        const int ch = std::max(def, std::min(tune->gram_pairs, 4096 / std::max(d.l3, 1)));
+        int ch = def;
+        if (tune && tune->gram_pairs > GRAM_CH) ch = std::max(def, std::min(tune->gram_pairs, 4096 / std::max(d.l3, 1)));
+        else if (small) ch = gram_pairs_small(d.l3, d.J, d.n_i2t);
         if (ch == def) continue;
         d.gram_ch = ch;
         d.ntile[KIND_GRAM] = (d.l1 * d.l2 + ch - 1) / ch;

@@ -151,10 +151,45 @@ __device__ __forceinline__ T* uniform_ptr(T* p) {
     return (T*)(((unsigned long long)hi << 32) | lo);
 }
 
-__device__ __forceinline__ int find_problem(const int* __restrict__ starts, int count, int b) {
-    // largest p with starts[p] <= b (starts has count+1 entries, starts[0] = 0);
-    // every lane of a wave asks for the same b, and the answer is made
-    // wave-uniform
+// Pointers read from descriptors are generic; loads through them become flat
+// instructions (which also count against the LDS wait counter).  Tensor data
+// always lives in device global memory, so cast to the global address space.
+#define RTG_GLOBAL __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ const RTG_GLOBAL T* gptr(const T* p) {
+    return (const RTG_GLOBAL T*)p;
+}
+template <typename T>
+__device__ __forceinline__ RTG_GLOBAL T* gptr_w(T* p) {
+    return (RTG_GLOBAL T*)p;
+}
+
+// The problem that holds tile b of a batch (the largest p with starts[p] <= b;
+// starts has count + 1 entries, starts[0] = 0) and the tile's index in it.
+// Called by whole waves with the same b in every lane: each lane looks at one
+// entry, so that up to 64 problems take one load's latency instead of a chain
+// of six (every workgroup of every kernel starts with this), and a single
+// problem takes none.
+struct TileOf {
+    int p, tile;
+};
+__device__ __forceinline__ TileOf find_problem(const int* __restrict__ starts, int count, int b) {
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    int lo = 0, n = count, first = 0;
+    while (n > 1) {
+        const int step = (n + 63) >> 6;
+        const int at = lane * step;
+        const int v = at < n ? *gptr(starts + lo + at) : 0x7fffffff;
+        const int c = __builtin_popcountll(__ballot(v <= b)) - 1;   // entry 0 of the range is <= b
+        first = __builtin_amdgcn_readlane(v, c);
+        lo += c * step;
+        n = min(step, n - c * step);
+    }
+    return {lo, b - first};
+}
+
+// The same problem found by one lane alone.
+__device__ __forceinline__ int find_problem_1(const int* __restrict__ starts, int count, int b) {
     int lo = 0, hi = count - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
@@ -203,14 +238,14 @@ constexpr int FROB_CHUNK = 4096;
 __host__ __device__ inline int frob_wgs(long long n) { return (int)((n + FROB_CHUNK - 1) / FROB_CHUNK); }
 
 // Sketched-Gram workgroups whose pairs carry many partials (J channels x nt2
-// column tiles above 48 per buffer) and few finished values (l3 <= 16) finish
-// each pair with GRAM_SPL threads, each over a slice of the channels, and
-// take GRAM_CH_SPLIT pairs.
+// column tiles above 48 per buffer) and few finished values (l3 <= 16) take
+// GRAM_CH_SPLIT pairs and sum the channels in GRAM_SPL slices.
 constexpr int GRAM_SPL = 8;
 constexpr int GRAM_CH_SPLIT = 256 / GRAM_SPL;
 __host__ __device__ inline bool gram_split(int l3, int J, int nt2) { return J * nt2 > 48 && l3 <= 16; }
 
-// (a, b) pairs of the sketch owned by one sketched-Gram workgroup
+// (a, b) pairs of the sketch owned by one sketched-Gram workgroup, and by one
+// of a batch that leaves the chip idle with that many (build_plan)
 __host__ __device__ inline int gram_pairs_per_block(int l3, int J, int nt2) {
     if (gram_split(l3, J, nt2)) return GRAM_CH_SPLIT;
     int ch = 4096 / (l3 > 0 ? l3 : 1);
@@ -218,24 +253,16 @@ __host__ __device__ inline int gram_pairs_per_block(int l3, int J, int nt2) {
     if (ch < 1) ch = 1;
     return ch;
 }
+constexpr int GRAM_CH_SMALL = 64;
+__host__ __device__ inline int gram_pairs_small(int l3, int J, int nt2) {
+    const int ch = gram_pairs_per_block(l3, J, nt2);
+    return ch < GRAM_CH_SMALL ? ch : GRAM_CH_SMALL;
+}
 
 // bfloat16 values are handled as raw 16-bit patterns (round to nearest even)
 __device__ __forceinline__ float bf2f(bf16_t u) { return __uint_as_float((unsigned)u << 16); }
 // round to nearest even (v_cvt_pk_bf16_f32 on gfx950; NaN stays NaN)
 __device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
-
-// Pointers read from descriptors are generic; loads through them become flat
-// instructions (which also count against the LDS wait counter).  Tensor data
-// always lives in device global memory, so cast to the global address space.
-#define RTG_GLOBAL __attribute__((address_space(1)))
-template <typename T>
-__device__ __forceinline__ const RTG_GLOBAL T* gptr(const T* p) {
-    return (const RTG_GLOBAL T*)p;
-}
-template <typename T>
-__device__ __forceinline__ RTG_GLOBAL T* gptr_w(T* p) {
-    return (RTG_GLOBAL T*)p;
-}
 
 // Mode-2 contraction of a column tile's mode-1 results (the second factor
 // of the sketch, Sec. 3.1): for the stacked row tiles t < NRT,

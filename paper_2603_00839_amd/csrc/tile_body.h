@@ -100,9 +100,9 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
     float* Xf = (float*)smem;                   // float32 tile
     float* Ys = (float*)smem;                   // mode-1 results (after the last super-block)
 
-    const int p = find_problem(starts, count, b);
-    const Desc& d = descs[p];
-    const int tile = uniform_int(b - starts[p]);
+    const TileOf at = find_problem(starts, count, b);
+    const Desc& d = descs[at.p];
+    const int tile = at.tile;
     const bool newv = (mode == TM_NEWV || mode == TM_GKNEW || mode == TM_NEWV1);
     // V_1 stored by the operator kernel already: sketched from the basis
     const bool v1_stored = (mode == TM_NEWV1) && d.X0 != nullptr;
