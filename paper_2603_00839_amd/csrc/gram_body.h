@@ -155,7 +155,7 @@ __device__ __forceinline__ void finish_sketches(const Desc& d, int q0, int qn, b
     typedef float f4v __attribute__((ext_vector_type(4)));
     const int tid = block_tid();
     const int L12 = d.l1 * d.l2;
-    const int J = d.J, nt2 = d.n_i2t, l3 = d.l3;
+    const int J = d.J, nt2 = d.n_i2t * d.nrs, l3 = d.l3;   // (partials of a channel)
     const int l3g = (l3 + 3) >> 2;                       // groups of four finished values
     const int al = L12 | q0 | qn;
     const int CH = (qn + 3) & ~3;                        // row length of Q

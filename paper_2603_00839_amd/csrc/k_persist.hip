@@ -63,7 +63,7 @@ constexpr int cmax(int a, int b) { return a > b ? a : b; }
 template <int R, bool TP, bool MB>
 struct PersistLds {
     static constexpr int PHI = PhiLayout<R, 4, SL_VEC>::FLOATS * 4;
-    static constexpr int TILE = cmax((int)sizeof(TileShared<MB, false, 4>), (int)sizeof(TileShared<MB, MB, 4>));
+    static constexpr int TILE = cmax((int)sizeof(TileShared<MB, false, 4, 128>), (int)sizeof(TileShared<MB, MB, 4, 128>));
     static constexpr int BYTES = cmax(cmax(PHI, TILE), (int)sizeof(GramSmem));
 };
 
@@ -251,11 +251,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
             // a float32 source in the mixed form is split into two bfloat16
             // planes (R0); new basis tensors take one plane
             if (MB && k.mode == TM_SKETCH_SRC)
-                tile_task<false, MB, MB, 4>(descs, starts, a.count, k.mode, 0, 0, 0, k.b,
-                                            *(TileShared<MB, MB, 4>*)lds);
+                tile_task<false, MB, MB, 4, 128>(descs, starts, a.count, k.mode, 0, 0, 0, k.b,
+                                            *(TileShared<MB, MB, 4, 128>*)lds);
             else
-                tile_task<false, MB, false, 4>(descs, starts, a.count, k.mode, k.arg, k.arg, 0, k.b,
-                                               *(TileShared<MB, false, 4>*)lds);
+                tile_task<false, MB, false, 4, 128>(descs, starts, a.count, k.mode, k.arg, k.arg, 0, k.b,
+                                               *(TileShared<MB, false, 4, 128>*)lds);
         } else {
             gram_task<false>(descs, starts, a.count, k.mode, k.arg, nullptr, k.b, *(GramSmem*)lds);
         }

@@ -67,16 +67,36 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 struct Layout {
     size_t V, W, PW, PV, SV, dots, G, H, R, gv, coef, y, state, scal, ot1, ot1h, ot2, ot3, total;
-    int n_i2t, ntile_tile, ntile_gram, ntile_phi;
+    int n_i2t, ntile_tile, ntile_gram, ntile_phi, nrs, prow;
 };
 
-Layout problem_layout(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16) {
+// Column tiles of a problem (workgroups of the tile kernel before its row parts).
+long long col_tiles(const rtg_op_s* op) { return (long long)op->J * ((op->I2 + TILE_TC - 1) / TILE_TC); }
+
+// Rows per part of a column tile of the tile kernel, for a batch of `total`
+// column tiles: halves where the batch has at most half as many column tiles
+// as the chip has compute units, whole columns otherwise.  A part writes its
+// own partial sketches, which the Gram kernel reads back, so more parts cost
+// more than idle units do: one 512x512x3 problem (48 column tiles, m = 50)
+// takes 3.65 ms with whole columns, 3.03 with halves, 3.11 with quarters and
+// 3.5 with eighths; eight problems (384 tiles, general PSF, m = 40) 7.4 ms with
+// whole columns and 7.5 with halves.
+constexpr long long PART_TILES = 128;
+int part_rows(const rtg_op_s* op, long long total) {
+    const int blocks = (op->I1 + 63) / 64;
+    return 64 * (total <= PART_TILES ? (blocks + 1) / 2 : blocks);
+}
+int whole_rows(const rtg_op_s* op) { return (op->I1 + 63) / 64 * 64; }
+
+Layout problem_layout(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, long long total) {
     Layout L{};
     const size_t n = (size_t)op->I1 * op->I2 * op->J;
     const size_t Ls = (size_t)sk->l1 * sk->l2 * sk->l3;
     const size_t es = bf16 ? 2 : 4;
     L.n_i2t = (op->I2 + TILE_TC - 1) / TILE_TC;
-    L.ntile_tile = op->J * L.n_i2t;
+    L.prow = bf16 || total <= 0 ? whole_rows(op) : part_rows(op, total);
+    L.nrs = (op->I1 + L.prow - 1) / L.prow;
+    L.ntile_tile = op->J * L.n_i2t * L.nrs;
     const int ch = gram_pairs_per_block(sk->l3, op->J, L.n_i2t);
     L.ntile_gram = sk->identity ? frob_wgs((long long)n) : (sk->l1 * sk->l2 + ch - 1) / ch;
     L.ntile_phi = phi_tiles(op->I1, op->I2, op->J, phi_jt(op->J));
@@ -158,8 +178,8 @@ void fill_gk_sides(Desc& d, Desc& u, const rtg_op_s* op, const rtg_sk_s* sk, int
     u.SVx = d.SV;
 }
 
-size_t problem_bytes(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, int method) {
-    size_t b = problem_layout(op, sk, m, bf16).total;
+size_t problem_bytes(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, int method, long long total) {
+    size_t b = problem_layout(op, sk, m, bf16, total).total;
     if (method == RTG_METHOD_GOLUB_KAHAN) b += gk_extra_layout(op, sk, m, bf16).total;
     return b;
 }
@@ -195,6 +215,8 @@ void fill_desc(Desc& d, const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16,
     d.skbf = bf16;
     d.has_om3 = sk->has_om3;
     d.n_i2t = L.n_i2t;
+    d.nrs = L.nrs;
+    d.prow = L.prow;
     d.ntile[KIND_PHI] = L.ntile_phi;
     d.ntile[KIND_TILE] = L.ntile_tile;
     d.ntile[KIND_GRAM] = L.ntile_gram;
@@ -315,6 +337,7 @@ struct Plan {
     int step_toep;     // fused step: Toeplitz taps
     int tile_rows;     // sketch tiles per wave of the tile kernel (2 where they fit, or 4)
     int step_rows;     // the same for the fused step
+    int block_rows;    // rows per block of the tile kernel
     int skbf;          // sketch contractions on bfloat16 operands (every problem's descriptor says so)
     Desc* d_desc_r;    // restart cycles: the descriptors with X0 = X (null without restarts)
     int persist;       // the Arnoldi process as one persistent launch
@@ -339,9 +362,10 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
     // many, at most 4096 finished values per workgroup.  Otherwise 256, or 64
     // where the batch then still has at most GRAM_SMALL_WGS workgroups: a
     // workgroup is a chain of latencies whose middle part goes with its pairs,
-    // and a few hundred workgroups run side by side.  (One 512x512x3 problem:
-    // 16 workgroups of 256 pairs or 64 of 64.)
-    constexpr long long GRAM_SMALL_WGS = 1024;
+    // and 512 workgroups run side by side, two per compute unit.  (Solves with
+    // 480 workgroups of 64 pairs 6.32 ms, with 256 pairs 6.50; with 512 of 64
+    // 7.44 against 7.55; with 680 of 64 0.88 against 0.84.)
+    constexpr long long GRAM_SMALL_WGS = 512;
     long long small_wgs = 0;
     for (auto& d : descs)
         if (!d.unsketched) {
@@ -360,6 +384,33 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
         d.gram_ch = ch;
         d.ntile[KIND_GRAM] = (d.l1 * d.l2 + ch - 1) / ch;
     }
+    // (bfloat16 products: whole columns, so that a sketch's sums keep their order)
+    for (auto& d : descs)
+        if (d.skbf && d.nrs > 1) {
+            d.ntile[KIND_TILE] /= d.nrs;
+            d.nrs = 1;
+            d.prow = (d.I1 + 63) / 64 * 64;
+        }
+    // rows per block of the tile kernel: 256 reads whole kilobytes of a
+    // column per wave and term (32 problems of 512x512x3, m = 50: 32.6 ms a
+    // solve, 33.1 with 128 rows, 34.4 with 64), 64 or 128 where no column is
+    // longer; for the one-term passes of Golub-Kahan, where nothing is gained
+    // from a term's length, 64 where 256 would pad the columns by more than a
+    // twentieth (12 problems of 328x501x3: 6.33 against 6.71 ms; 20 of
+    // 512x512x3: 9.49 against 8.82)
+    int max_i1 = 0;
+    long long rows = 0, padded = 0;
+    for (auto& d : descs) {
+        max_i1 = std::max(max_i1, d.I1);
+        rows += d.I1;
+        padded += (d.I1 + 255) / 256 * 256;
+    }
+    plan.block_rows = max_i1 <= 64 ? 64 : (max_i1 <= 128 ? 128 : 256);
+    if (nsides > 1 && 20 * (padded - rows) > rows) plan.block_rows = 64;
+    // (the mixed form's tile is a third more registers: 128 keeps two
+    // workgroups per compute unit.  31 problems of 480x313x3: 1.17 ms, with 256
+    // rows 1.33)
+    if (!descs.empty() && descs[0].skbf && !descs[0].bf16) plan.block_rows = std::min(plan.block_rows, 128);
     plan.rmax = 1;
     for (int k = 0; k < NKIND; ++k) {
         int acc = 0;
@@ -530,19 +581,19 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_X0, 0, plan.rmax, plan.phi_jt, 0,
                                     s, plan.stencil, plan.phi_dma, plan.phi_toep));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, nullptr, s, us));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         for (int j = 1; j <= mmax; ++j) {
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                     plan.phi_jt, bf16, s, plan.stencil, plan.phi_dma, plan.phi_toep));
             RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, nullptr, s, us));
             if (j < mmax || last_newv)
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
-                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         }
         if (solve) {
             RTG_TIMED(3, launch_solve(dd, count, mmax, s));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0,
-                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         }
         return RTG_OK;
     }
@@ -553,23 +604,23 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_X0, 0, plan.rmax, plan.phi_jt, 0,
                                     s, 1, plan.phi_dma, plan.phi_toep));
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0,
-                                 plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+                                 plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, nullptr, s));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         for (int j = 1; j <= mmax; ++j) {
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                     plan.phi_jt, bf16, s, 1, plan.phi_dma, plan.phi_toep));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_W, 0, 0, bf16, 0,
-                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
             RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, nullptr, s));
             if (j < mmax || last_newv)
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
-                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         }
         if (solve) {
             RTG_TIMED(3, launch_solve(dd, count, mmax, s));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0,
-                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         }
         return RTG_OK;
     }
@@ -596,7 +647,7 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
         if (solve) {
             RTG_TIMED(3, launch_solve(dd, count, mmax, s));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0,
-                                     plan.tile_rows, plan.skbf));
+                                     plan.tile_rows, plan.skbf, plan.block_rows));
         }
         return RTG_OK;
     }
@@ -608,12 +659,12 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
         // V_1 = R0 (scale 1, set by the init kernel) with both its sketches
         // in one pass (stored there too where X0 is absent, R0 = C); the
         // start step takes beta from S(V_1)
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV1, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV1, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, nullptr, s));
     } else {
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, nullptr, s));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
     }
     for (int j = 1; j <= mmax; ++j) {
         // S(V_j) and S(Phi(V_j)) come from the pass that formed V_j.  With a
@@ -632,13 +683,13 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
                 RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                         plan.phi_jt, bf16, s, 0, plan.phi_dma, plan.phi_toep));
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
-                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
             }
         }
     }
     if (solve) {
         RTG_TIMED(3, launch_solve(dd, count, mmax, s));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
     }
     return RTG_OK;
 }
@@ -661,25 +712,25 @@ int run_gk(const Plan& plan, int count, int mmax, int bf16, bool any_x0, bool so
     RTG_HIP(launch_compose(plan.d_desc, 2 * count, plan.compose_max, s));
     if (any_x0) RTG_TIMED(0, launch_phi(dV, sp, count, tp, PS_X0, 0, plan.rmax, plan.phi_jt, 0, s, 0, plan.phi_dma, plan.phi_toep));
     // beta_1 = ||R0||_Theta, U_1 = R0 / beta_1 (with S(U_1) and S(Phi^T(U_1)))
-    RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows));
+    RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.block_rows));
     RTG_TIMED(2, launch_gram(dU, sg, count, tg, GM_START, 0, nullptr, s));
-    RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows));
+    RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.block_rows));
     for (int c = 1; c <= mmax; ++c) {
         // alpha_c; V_c = (Phi^T(U_c) - beta_c V_{c-1}) / alpha_c
         RTG_TIMED(2, launch_gram(dU, sg, count, tg, GM_GK, c, nullptr, s));
         RTG_TIMED(0, launch_phi(dU, sp, count, tp, PS_BASIS, c - 1, plan.rmax, plan.phi_jt, bf16, s, 0, plan.phi_dma, plan.phi_toep));
         RTG_TIMED(1, launch_tile(dV, st, count, tt, TM_GKNEW, c - 1, c - 1, bf16, 0, plan.l1max, s,
-                                 c >= 2 ? c - 2 : 0));
+                                 c >= 2 ? c - 2 : 0, plan.tile_rows, 0, plan.block_rows));
         // beta_{c+1}, column c of B, Givens and stop test; U_{c+1} = (Phi(V_c) - alpha_c U_c) / beta_{c+1}
         RTG_TIMED(2, launch_gram(dV, sg, count, tg, GM_GK, c, nullptr, s));
         if (c < mmax || !solve) {   // the bidiagonalisation alone also forms U_{m+1}
             RTG_TIMED(0, launch_phi(dV, sp, count, tp, PS_BASIS, c - 1, plan.rmax, plan.phi_jt, bf16, s, 0, plan.phi_dma, plan.phi_toep));
-            RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_GKNEW, c, c, bf16, 0, plan.l1max, s, c - 1, plan.tile_rows));
+            RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_GKNEW, c, c, bf16, 0, plan.l1max, s, c - 1, plan.tile_rows, 0, plan.block_rows));
         }
     }
     if (solve) {
         RTG_TIMED(3, launch_solve(dV, count, mmax, s));
-        RTG_TIMED(1, launch_tile(dV, st, count, tt, TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows));
+        RTG_TIMED(1, launch_tile(dV, st, count, tt, TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.block_rows));
     }
     return RTG_OK;
 }
@@ -986,7 +1037,7 @@ int rtg_sketch(rtg_sk sk, int x_dtype, const void* X, float* SX, void* ws, size_
     }
     rtg_op_s dummy{sk->I1, sk->I2, sk->J, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr,
                    {nullptr, nullptr, nullptr}, 0, nullptr, nullptr};
-    Layout L = problem_layout(&dummy, sk, 1, x_dtype == RTG_BF16);
+    Layout L = problem_layout(&dummy, sk, 1, x_dtype == RTG_BF16, 0);
     std::vector<Desc> descs(1);
     fill_desc(descs[0], &dummy, sk, 1, x_dtype == RTG_BF16, nullptr, L);
     descs[0].PW = (float*)((char*)ws + plan_bytes(1));
@@ -997,7 +1048,8 @@ int rtg_sketch(rtg_sk sk, int x_dtype, const void* X, float* SX, void* ws, size_
     int rc = build_plan(descs, ws, s, plan);
     if (rc) return rc;
     RTG_HIP(launch_tile(plan.d_desc, starts_of(plan, KIND_TILE, 1), 1, plan.total[KIND_TILE], TM_SKETCH_SRC,
-                        0, 0, x_dtype == RTG_BF16, x_dtype == RTG_BF16, plan.l1max, s, 0, plan.tile_rows));
+                        0, 0, x_dtype == RTG_BF16, x_dtype == RTG_BF16, plan.l1max, s, 0, plan.tile_rows, 0,
+                        plan.block_rows));
     RTG_HIP(launch_gram(plan.d_desc, starts_of(plan, KIND_GRAM, 1), 1, plan.total[KIND_GRAM], GM_SKETCH_OUT,
                         0, SX, s));
     return RTG_OK;
@@ -1065,14 +1117,14 @@ int rtg_sketch_noalloc(rtg_sk sk, int x_dtype, const void* X, float* SX, void* s
 size_t rtg_workspace_bytes(rtg_op op, rtg_sk sk, int m, int basis_dtype) {
     if (check_pair(op, sk) || check_m(sk, m)) return 0;
     // (room for the restart-cycle descriptor copy of rtg_solve with restarts)
-    return plan_bytes(1, 1, true) + problem_layout(op, sk, m, basis_dtype == RTG_BF16).total;
+    return plan_bytes(1, 1, true) + problem_layout(op, sk, m, basis_dtype == RTG_BF16, col_tiles(op)).total;
 }
 
 int rtg_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t* v_offset, size_t* sv_offset) {
     int rc = check_pair(op, sk);
     if (rc) return rc;
     if ((rc = check_m(sk, m))) return rc;
-    Layout L = problem_layout(op, sk, m, basis_dtype == RTG_BF16);
+    Layout L = problem_layout(op, sk, m, basis_dtype == RTG_BF16, col_tiles(op));
     if (v_offset) *v_offset = plan_bytes(1) + L.V;
     if (sv_offset) *sv_offset = plan_bytes(1) + L.SV;
     return RTG_OK;
@@ -1089,7 +1141,7 @@ int rtg_arnoldi(rtg_op op, rtg_sk sk, const float* R0, int m, int basis_dtype, d
     const int bf16 = basis_dtype == RTG_BF16;
     if (ws_bytes < rtg_workspace_bytes(op, sk, m, basis_dtype)) return RTG_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    Layout L = problem_layout(op, sk, m, bf16);
+    Layout L = problem_layout(op, sk, m, bf16, col_tiles(op));
     std::vector<Desc> descs(1);
     fill_desc(descs[0], op, sk, m, bf16, (char*)ws + plan_bytes(1), L);
     descs[0].R0src = R0;
@@ -1112,18 +1164,23 @@ size_t rtg_batch_workspace_bytes(int count, const rtg_problem* probs) {
     bool restart = false;
     for (int p = 0; p < count; ++p) restart = restart || probs[p].params.restarts > 0;
     size_t total = plan_bytes(count, method == RTG_METHOD_GOLUB_KAHAN ? 2 : 1, restart);
+    long long tiles = 0;
     for (int p = 0; p < count; ++p) {
         const rtg_problem& q = probs[p];
         if (check_pair(q.op, q.sk) || check_m(q.sk, q.params.m)) return 0;
         if (q.params.method != method) return 0;
-        total += problem_bytes(q.op, q.sk, q.params.m, q.params.basis_dtype == RTG_BF16, method);
+        tiles += col_tiles(q.op);
+    }
+    for (int p = 0; p < count; ++p) {
+        const rtg_problem& q = probs[p];
+        total += problem_bytes(q.op, q.sk, q.params.m, q.params.basis_dtype == RTG_BF16, method, tiles);
     }
     return total;
 }
 
 size_t rtg_gk_workspace_bytes(rtg_op op, rtg_sk sk, int m, int basis_dtype) {
     if (check_pair(op, sk) || check_m(sk, m)) return 0;
-    return plan_bytes(1, 2) + problem_bytes(op, sk, m, basis_dtype == RTG_BF16, RTG_METHOD_GOLUB_KAHAN);
+    return plan_bytes(1, 2) + problem_bytes(op, sk, m, basis_dtype == RTG_BF16, RTG_METHOD_GOLUB_KAHAN, col_tiles(op));
 }
 
 int rtg_gk_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t* v_offset, size_t* u_offset) {
@@ -1131,7 +1188,7 @@ int rtg_gk_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t
     if (rc) return rc;
     if ((rc = check_m(sk, m))) return rc;
     const int bf16 = basis_dtype == RTG_BF16;
-    const Layout L = problem_layout(op, sk, m, bf16);
+    const Layout L = problem_layout(op, sk, m, bf16, col_tiles(op));
     const GKExtra E = gk_extra_layout(op, sk, m, bf16);
     if (v_offset) *v_offset = plan_bytes(1, 2) + L.V;
     if (u_offset) *u_offset = plan_bytes(1, 2) + L.total + E.V;
@@ -1150,7 +1207,7 @@ int rtg_golub_kahan(rtg_op op, rtg_sk sk, const float* R0, int m, int basis_dtyp
     const int bf16 = basis_dtype == RTG_BF16;
     if (ws_bytes < rtg_gk_workspace_bytes(op, sk, m, basis_dtype)) return RTG_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    const Layout L = problem_layout(op, sk, m, bf16);
+    const Layout L = problem_layout(op, sk, m, bf16, col_tiles(op));
     char* base = (char*)ws + plan_bytes(1, 2);
     std::vector<Desc> descs(2);
     fill_desc(descs[0], op, sk, m, bf16, base, L);
@@ -1204,14 +1261,18 @@ int prepare_batch(int count, const rtg_problem* probs, void* ws, size_t ws_bytes
     bt.skbf = basis != RTG_F32;
     bt.nsides = gk ? 2 : 1;
     bt.rmax = 0;
-    for (int p = 0; p < count; ++p) bt.rmax = std::max(bt.rmax, probs[p].params.restarts);
+    long long tiles = 0;
+    for (int p = 0; p < count; ++p) {
+        bt.rmax = std::max(bt.rmax, probs[p].params.restarts);
+        tiles += col_tiles(probs[p].op);
+    }
     bt.descs.assign((size_t)count * bt.nsides, Desc{});
     size_t off = plan_bytes(count, bt.nsides, bt.rmax > 0);
     bt.mmax = 0;
     bt.any_x0 = false;
     for (int p = 0; p < count; ++p) {
         const rtg_problem& q = probs[p];
-        Layout L = problem_layout(q.op, q.sk, q.params.m, bf16);
+        Layout L = problem_layout(q.op, q.sk, q.params.m, bf16, tiles);
         char* base = (char*)ws + off;
         Desc& d = bt.descs[p];
         fill_desc(d, q.op, q.sk, q.params.m, bf16, base, L);

@@ -53,6 +53,8 @@ struct Desc {
                         // float32 basis of the mixed form RTG_F32_BF16)
     int has_om3;        // Om3 given (else identity, l3 == J)
     int n_i2t;          // ceil(I2 / TILE_TC)
+    int nrs;            // row parts of a column tile: workgroups (and partials) per column tile
+    int prow;           // rows of a part (a multiple of 64; nrs = ceil(I1 / prow))
     int ntile[NKIND];   // tiles of this problem per kernel kind
     int mu_fixed;       // 1: mu given, 0: chosen by mu_rule
     int mu_rule;        // RTG_MU_DISCREPANCY or RTG_MU_GCV
@@ -380,6 +382,87 @@ __device__ __forceinline__ void mode2_partials4(const float* Ys, int wave, int l
         for (int t = 0; t < RT; ++t) one(RT + t, B1, P1, 16 * t + m16);
 }
 
+// The same for every l2 <= 128 (LMAX_SPATIAL): wave w takes the column tiles w
+// and w + 4 of Om2 and of Om2 A2, all requested together before the mode-1
+// results go to LDS.  (The general loop above waits for a column tile's
+// entries at each change of tile or matrix: 12 waits of about 0.7 us for
+// l2 = 72.)
+template <int TC>
+struct Mode2Ops {
+    float B[2][2][TC / 4];   // [column tile w or w + 4][Om2 or Om2 A2]
+};
+template <int TC>
+__device__ __forceinline__ void mode2_load(Mode2Ops<TC>& o, int wave, int lane, int l2, int I2, int i20, int ncol,
+                                           int NRT, int RT, const float* om2, const float* om2t) {
+    static_assert(LMAX_SPATIAL <= 128, "eight column tiles of 16");
+    const int m16 = lane & 15, kq = lane >> 4;
+    const int obytes = l2 * I2 * 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h == 1 && NRT <= RT) break;                  // a sketch-only pass has no composed matrices
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(h ? om2t : om2), (short)0, obytes, 0x00020000);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (16 * (wave + 4 * c) >= l2) break;
+            const int bcol = 16 * (wave + 4 * c) + m16;
+#pragma unroll
+            for (int ks = 0; ks < TC / 4; ++ks) {
+                const int k = 4 * ks + kq;
+                const unsigned off = (bcol < l2 && k < ncol) ? (unsigned)(bcol * I2 + i20 + k) * 4u : 0x80000000u;
+                o.B[c][h][ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+            }
+        }
+    }
+}
+template <int TC, int YP>
+__device__ __forceinline__ void mode2_partials_all(const float* Ys, const Mode2Ops<TC>& o, int wave, int lane, int NRT,
+                                                   int RT, int l1, int l2, float* P0, float* P1) {
+    typedef float f4v __attribute__((ext_vector_type(4)));
+    const int m16 = lane & 15, kq = lane >> 4;
+    const bool one = 16 * wave < l2, two = 16 * (wave + 4) < l2;
+    if (!one) return;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h == 1 && NRT <= RT) break;
+        float* P = h ? P1 : P0;
+        for (int t = 0; t < RT; ++t) {
+            // a row tile's results are read once for both column tiles, whose
+            // product chains run side by side
+            float y[TC / 4];
+#pragma unroll
+            for (int ks = 0; ks < TC / 4; ++ks) y[ks] = Ys[(16 * (t + (h ? RT : 0)) + m16) * YP + 4 * ks + kq];
+            f4v p[2] = {f4v{0.f, 0.f, 0.f, 0.f}, f4v{0.f, 0.f, 0.f, 0.f}};
+            if (two) {
+#pragma unroll
+                for (int ks = 0; ks < TC / 4; ++ks)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        p[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.B[c][h][ks], y[ks], p[c], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < TC / 4; ++ks)
+                    p[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.B[0][h][ks], y[ks], p[0], 0, 0, 0);
+            }
+            const int ar = 16 * t + m16;
+            if (ar < l1) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    if (c == 1 && !two) break;
+                    const int b0 = 16 * (wave + 4 * c) + 4 * kq;
+                    float* q = P + (size_t)ar * l2 + b0;
+                    if ((l2 & 3) == 0) {
+                        if (b0 < l2) *gptr_w((f4v*)q) = p[c];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (b0 + i < l2) *gptr_w(q + i) = p[c][i];
+                    }
+                }
+            }
+        }
+    }
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
@@ -403,7 +486,8 @@ hipError_t launch_phi_single(int I1, int I2, int J, int r1, int r2, int rB, cons
                              const void* src, int bf16_in, const float* C, float* dst, hipStream_t s);
 hipError_t launch_tile(const Desc* d, const int* starts, int count, int total_tiles,
                        int mode, int nterms, int dst_index, int basis_bf16, int src_bf16,
-                       int l1max, hipStream_t s, int first_term = 0, int rows = 2, int sketch_bf16 = 0);
+                       int l1max, hipStream_t s, int first_term = 0, int rows = 2, int sketch_bf16 = 0,
+                       int block_rows = 256);
 // rows (tile and step kernels): 16-row sketch tiles per wave, 2 where the
 // stacked sketch rows fit (the default), or 4
 hipError_t launch_step(const Desc* d, const int* starts, int count, int total_tiles, int j, int rmax,

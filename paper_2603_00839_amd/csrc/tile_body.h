@@ -23,15 +23,17 @@
 // product with (A1, A2, B^T) (eq. (2)).  The next step's sketched inner
 // products then need no separate pass over W = Phi(V_{j+1}).
 //
-// Phase 1 (per super-block of 256 rows): every lane owns 32 elements of the
+// Phase 1 (per block of SBR rows): every lane owns SBR / 8 elements of the
 // tile, accumulates the multi-AXPY in float32 registers, stores the result
 // (rounded to bfloat16 for a bfloat16 basis) and writes it to LDS, column-
-// major.  Phase 2: the four waves split the (stacked) sketch rows and run the
+// major.  Terms go in groups, two groups in flight: 16 to 32 KB per workgroup
+// (one 512x512x3 problem has 48 workgroups and is bound by their latency:
+// 63 -> 45 us per launch against one term in two halves).  Phase 2: the four waves split the (stacked) sketch rows and run the
 // mode-1 contraction on MFMA with the tile from LDS as the B operand
 // (v_mfma_f32_16x16x4f32 for a float32 basis, v_mfma_f32_16x16x32_bf16 for a
 // bfloat16 one; a float32 tile in bfloat16 mode is split into high and low
 // bfloat16 planes, and so is the composed matrix Om1 A1).  After the last
-// super-block the mode-2 contraction is a second small MFMA product, and the
+// block the mode-2 contraction is a second small MFMA product, and the
 // partial P of every tile goes to a buffer that the sketched-Gram kernel
 // reduces (applying mode 3).
 
@@ -44,7 +46,6 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u2v __attribute__((ext_vector_type(2)));
 
-constexpr int TILE_SBR = 256;   // rows per super-block: 256 lanes x 32 elements / 32 columns
 // element offset of a chunk outside the tile: its byte offset lies past every
 // buffer extent used here (a tile spans 32 x I1 elements of at most 4 bytes)
 constexpr unsigned OOB_ELEM = 0x20000000u;
@@ -57,11 +58,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, in
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes, 0x00020000);
 }
 
-template <bool MB, bool SPLIT, int RPW>
+template <bool MB, bool SPLIT, int RPW, int SBR>
 struct TileSmem {
     static constexpr int TC = TILE_TC;
-    static constexpr int CSB = TILE_SBR + 8;    // bfloat16 plane column stride (elements)
-    static constexpr int CSF = TILE_SBR + 4;    // float32 column stride (elements)
+    static constexpr int CSB = SBR + 8;         // bfloat16 plane column stride (elements)
+    static constexpr int CSF = SBR + 4;         // float32 column stride (elements)
     static constexpr int XBYTES = MB ? (SPLIT ? 2 : 1) * TC * CSB * 2 : TC * CSF * 4;
     static constexpr int YP = TC + 1;
     static constexpr int YBYTES = 64 * RPW * YP * 4;   // stacked sketch rows x columns
@@ -69,10 +70,10 @@ struct TileSmem {
 };
 
 // LDS of one tile workgroup
-template <bool MB, bool SPLIT, int RPW>
+template <bool MB, bool SPLIT, int RPW, int SBR>
 struct TileShared {
     float coef_s[MMAX + 2];
-    __attribute__((aligned(16))) unsigned char smem[TileSmem<MB, SPLIT, RPW>::BYTES];
+    __attribute__((aligned(16))) unsigned char smem[TileSmem<MB, SPLIT, RPW, SBR>::BYTES];
 };
 
 // BB: basis stored as bfloat16; MB: the sketch contractions take bfloat16
@@ -80,17 +81,18 @@ struct TileShared {
 // float32 basis in the mixed form (RTG_F32_BF16) does with its tile rounded
 // to bfloat16 for the products; SPLIT: the sketched tile is float32 in
 // bfloat16 mode, split into two planes; RPW: sketch row tiles of 16 per wave.
-template <bool BB, bool MB, bool SPLIT, int RPW>
+template <bool BB, bool MB, bool SPLIT, int RPW, int SBR>
 __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const int* __restrict__ starts,
                                           int count, int mode, int nterms_arg, int dst_index, int t0, int b,
-                                          TileShared<MB, SPLIT, RPW>& sh) {
+                                          TileShared<MB, SPLIT, RPW, SBR>& sh) {
     static_assert(MB || !BB, "a bfloat16 basis uses bfloat16 products");
-    using SM = TileSmem<MB, SPLIT, RPW>;
+    using SM = TileSmem<MB, SPLIT, RPW, SBR>;
     constexpr int TC = TILE_TC;
-    constexpr int SBR = TILE_SBR;
     constexpr int CK = BB ? 8 : 4;             // elements per lane chunk (16 bytes of basis)
-    constexpr int NCK = SBR * TC / 256 / CK;   // chunks per lane
+    constexpr int NCK = SBR * TC / 256 / CK;   // chunks per lane and term
     constexpr int KBR = MB ? 32 : 16;          // rows per MFMA K-block
+    constexpr int NKB = SBR / KBR;             // K-blocks per block
+    constexpr int GT = NCK >= (BB ? 4 : 8) ? 1 : (NCK >= (BB ? 2 : 4) ? 2 : 4);   // terms per group, two groups in flight
     constexpr int CSB = SM::CSB, CSF = SM::CSF, YP = SM::YP;
 
     float* coef_s = sh.coef_s;
@@ -98,7 +100,7 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
     bf16_t* Xh = (bf16_t*)smem;                 // high (or only) bfloat16 plane
     bf16_t* Xl = Xh + TC * CSB;                 // low plane (SPLIT)
     float* Xf = (float*)smem;                   // float32 tile
-    float* Ys = (float*)smem;                   // mode-1 results (after the last super-block)
+    float* Ys = (float*)smem;                   // mode-1 results (after the last block)
 
     const TileOf at = find_problem(starts, count, b);
     const Desc& d = descs[at.p];
@@ -117,7 +119,10 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
 
     const int I1 = d.I1, I2 = d.I2;
     const int l1 = d.l1, l2 = d.l2;
-    const int t2 = tile % d.n_i2t, c = tile / d.n_i2t;
+    // rows [row0, row1) of column tile t2 of channel c: the tile's row part
+    const int nrs = d.nrs, ct = tile / nrs;
+    const int t2 = ct % d.n_i2t, c = ct / d.n_i2t;
+    const int row0 = (tile - ct * nrs) * d.prow, row1 = min(I1, row0 + d.prow);
     const int i20 = t2 * TC;
     const int ncol = min(TC, I2 - i20);
     const size_t tile_off = (size_t)c * I1 * I2 + (size_t)i20 * I1;
@@ -159,7 +164,7 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
 #pragma unroll
         for (int g = 0; g < 2; ++g) acc[u][g] = f4{0.f, 0.f, 0.f, 0.f};
 
-    // chunk u of this lane: column col[u], rows row[u] .. row[u] + CK - 1 of the super-block
+    // chunk u of this lane: column col[u], rows row[u] .. row[u] + CK - 1 of the block
     int colu[NCK], rowu[NCK];
 #pragma unroll
     for (int u = 0; u < NCK; ++u) {
@@ -167,12 +172,10 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
         colu[u] = e / SBR;
         rowu[u] = e % SBR;
     }
+    const int tile_elems = ncol * I1;
 
-    const int nsb = (I1 + SBR - 1) / SBR;
-    for (int sb = 0; sb < nsb; ++sb) {
-        // ---- phase 1: multi-AXPY, store, LDS.  Loads are unconditional from
-        // clamped (always in-bounds) addresses and masked afterwards, so that
-        // they stay in flight together.
+    for (int r0 = row0; r0 < row1; r0 += SBR) {
+        // ---- phase 1: multi-AXPY, store, LDS.
         // Buffer loads and stores with per-lane byte offsets from a uniform
         // base: a chunk outside the tile gets an offset past the buffer's
         // extent, so the hardware returns zeros for its loads and drops its
@@ -180,76 +183,110 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
         unsigned offs[NCK];
 #pragma unroll
         for (int u = 0; u < NCK; ++u) {
-            const int rg = sb * SBR + rowu[u];
-            offs[u] = ((rg < I1) & (colu[u] < ncol)) ? (unsigned)(colu[u] * I1 + rg) : OOB_ELEM;
+            const int rg = r0 + rowu[u];
+            offs[u] = ((rg < row1) & (colu[u] < ncol)) ? (unsigned)(colu[u] * I1 + rg) : OOB_ELEM;
         }
-        const int tile_elems = ncol * I1;
+        // multi-AXPY in groups of GT terms: a group is under way while the
+        // one before it is applied
+        u4 v[2][GT][NCK];
+        const int ngr = (nterms - first + GT - 1) / GT;
+        auto load_group = [&](int g, u4 (&vg)[GT][NCK]) {
+#pragma unroll
+            for (int q = 0; q < GT; ++q) {
+                const int i = first + g * GT + q;
+                if (i >= nterms) break;
+                const auto rv = make_rsrc((const char*)d.V + ((size_t)i * d.n + tile_off) * es, tile_elems * (int)es);
+#pragma unroll
+                for (int u = 0; u < NCK; ++u)
+                    vg[q][u] = __builtin_amdgcn_raw_buffer_load_b128(rv, offs[u] * (unsigned)es, 0, 0);
+            }
+        };
         float x[NCK][CK];
-        if (src == nullptr) {
+        auto apply_group = [&](int g, const u4 (&vg)[GT][NCK]) {
 #pragma unroll
-            for (int u = 0; u < NCK; ++u)
+            for (int q = 0; q < GT; ++q) {
+                const int i = first + g * GT + q;
+                if (i >= nterms) break;
+                const float ci = coef_s[i];
 #pragma unroll
-                for (int q = 0; q < CK; ++q) x[u][q] = 0.f;
-        } else if (src_is_bf) {
-            const auto rs = make_rsrc((const char*)src + tile_off * 2, tile_elems * 2);
+                for (int u = 0; u < NCK; ++u)
 #pragma unroll
-            for (int u = 0; u < NCK; ++u) {
-                const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, offs[u] * 2u, 0, 0);
+                    for (int r = 0; r < 4; ++r) {
+                        if constexpr (BB) {
+                            x[u][2 * r] = fmaf(-ci, __uint_as_float(vg[q][u][r] << 16), x[u][2 * r]);
+                            x[u][2 * r + 1] = fmaf(-ci, __uint_as_float(vg[q][u][r] & 0xffff0000u), x[u][2 * r + 1]);
+                        } else {
+                            x[u][r] = fmaf(-ci, __uint_as_float(vg[q][u][r]), x[u][r]);
+                        }
+                    }
+            }
+        };
+        // the source first: the terms are applied to it in order
+        u4 xs[NCK][BB ? 2 : 1];
+        if (src != nullptr) {
+            if (src_is_bf) {
+                const auto rs = make_rsrc((const char*)src + tile_off * 2, tile_elems * 2);
 #pragma unroll
-                for (int q = 0; q < CK / 2; ++q) {
-                    x[u][2 * q] = __uint_as_float(v[q] << 16);
-                    x[u][2 * q + 1] = __uint_as_float(v[q] & 0xffff0000u);
+                for (int u = 0; u < NCK; ++u) xs[u][0] = __builtin_amdgcn_raw_buffer_load_b128(rs, offs[u] * 2u, 0, 0);
+            } else {
+                const auto rs = make_rsrc((const char*)src + tile_off * 4, tile_elems * 4);
+#pragma unroll
+                for (int u = 0; u < NCK; ++u)
+#pragma unroll
+                    for (int q = 0; q < CK / 4; ++q)
+                        xs[u][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, offs[u] * 4u + q * 16u, 0, 0);
+            }
+        }
+        if (ngr > 0) load_group(0, v[0]);
+        if (ngr > 1) load_group(1, v[1]);
+        // A fragments of this block's products in operand order: one
+        // contiguous 1 KB read per wave and tile; padding rows and columns
+        // are stored zeros, and unused tiles (t >= NRT) read nothing (offset
+        // past the buffer range)
+        struct AF {
+            u4 h, l;     // bfloat16 products: Om1 (h), or Om1 A1 high / low; float32: h as f4 bits
+        };
+        auto load_a = [&](int kb, AF* A) {
+            const int kbg = r0 / KBR + kb;           // (row parts start at multiples of 64)
+#pragma unroll
+            for (int u = 0; u < RPW; ++u) {
+                const int t = wave + 4 * u;
+                const bool half = t >= RT;
+                const int tl = t - (half ? RT : 0);
+                const unsigned off = (t < NRT) ? (unsigned)((tl * nkbf + kbg) * 64 + lane) * 16u : OOB_A;
+                const auto& rs = half ? rom1c : rom1;
+                A[u].h = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+                if constexpr (MB)
+                    A[u].l = half ? __builtin_amdgcn_raw_buffer_load_b128(rs, off + fbytes, 0, 0) : u4{0u, 0u, 0u, 0u};
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < NCK; ++u)
+#pragma unroll
+            for (int q = 0; q < CK / 4; ++q) {
+                if (src == nullptr) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[u][4 * q + r] = 0.f;
+                } else if (src_is_bf) {
+                    if constexpr (BB) {
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
+                            const unsigned w = xs[u][0][2 * q + r];
+                            x[u][4 * q + 2 * r] = __uint_as_float(w << 16);
+                            x[u][4 * q + 2 * r + 1] = __uint_as_float(w & 0xffff0000u);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[u][4 * q + r] = __uint_as_float(xs[u][q][r]);
                 }
             }
-        } else {
-            const auto rs = make_rsrc((const char*)src + tile_off * 4, tile_elems * 4);
-#pragma unroll
-            for (int u = 0; u < NCK; ++u)
-#pragma unroll
-                for (int q = 0; q < CK; q += 4) {
-                    const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, offs[u] * 4u + q * 4u, 0, 0);
-                    x[u][q] = __uint_as_float(v[0]); x[u][q + 1] = __uint_as_float(v[1]);
-                    x[u][q + 2] = __uint_as_float(v[2]); x[u][q + 3] = __uint_as_float(v[3]);
-                }
-        }
-        // multi-AXPY, software-pipelined: the next stage's loads are in
-        // flight while the current stage is applied.  A stage is one term
-        // (bfloat16 basis: 4 chunks) or half a term (float32: 4 of 8 chunks).
-        constexpr int SPT = BB ? 1 : 2;          // stages per term
-        constexpr int CPS = NCK / SPT;           // chunks per stage
-        const int nst = (nterms - first) * SPT;
-        auto load_stage = [&](int st, u4* v) {
-            const int i = first + st / SPT, c0 = (st % SPT) * CPS;
-            const auto rv = make_rsrc((const char*)d.V + ((size_t)i * d.n + tile_off) * es, tile_elems * (int)es);
-#pragma unroll
-            for (int u = 0; u < CPS; ++u)
-                v[u] = __builtin_amdgcn_raw_buffer_load_b128(rv, offs[c0 + u] * (unsigned)es, 0, 0);
-        };
-        auto apply_stage = [&](int st, const u4* v) {
-            const float ci = coef_s[first + st / SPT];
-            const int c0 = (st % SPT) * CPS;
-#pragma unroll
-            for (int uu = 0; uu < CPS; ++uu)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if constexpr (BB) {
-                        x[uu][2 * q] = fmaf(-ci, __uint_as_float(v[uu][q] << 16), x[uu][2 * q]);
-                        x[uu][2 * q + 1] = fmaf(-ci, __uint_as_float(v[uu][q] & 0xffff0000u), x[uu][2 * q + 1]);
-                    } else {
-                        // c0 is 0 or CPS: select the half with a uniform branch-free index
-                        float& xr = (c0 == 0) ? x[uu][q] : x[CPS + uu][q];
-                        xr = fmaf(-ci, __uint_as_float(v[uu][q]), xr);
-                    }
-                }
-        };
-        u4 va[CPS], vb[CPS];
-        if (nst > 0) load_stage(0, va);
-        for (int st = 0; st < nst; st += 2) {
-            if (st + 1 < nst) load_stage(st + 1, vb);
-            apply_stage(st, va);
-            if (st + 1 < nst) {
-                if (st + 2 < nst) load_stage(st + 2, va);
-                apply_stage(st + 1, vb);
+        for (int g = 0; g < ngr; g += 2) {
+            apply_group(g, v[0]);
+            if (g + 2 < ngr) load_group(g + 2, v[0]);
+            if (g + 1 < ngr) {
+                apply_group(g + 1, v[1]);
+                if (g + 3 < ngr) load_group(g + 3, v[1]);
             }
         }
         // scale (chunks outside the tile are zero already), round (bfloat16 basis), store
@@ -257,6 +294,12 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
         for (int u = 0; u < NCK; ++u)
 #pragma unroll
             for (int q = 0; q < CK; ++q) x[u][q] *= scale;
+        const int nkb = (min(SBR, row1 - r0) + KBR - 1) / KBR;
+        AF A0[RPW], A1[RPW];
+        if (do_sketch) {
+            load_a(0, A0);
+            if (nkb > 1) load_a(1, A1);
+        }
         if (newv && BB && do_store) {
             const auto rd = make_rsrc((const char*)d.V + ((size_t)dst_index * d.n + tile_off) * 2, tile_elems * 2);
 #pragma unroll
@@ -281,7 +324,7 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
                 }
         }
         if (!do_sketch) continue;
-        if (sb > 0) __syncthreads();          // the previous super-block's MFMA reads are done
+        if (r0 > row0) __syncthreads();       // the previous block's MFMA reads are done
 #pragma unroll
         for (int u = 0; u < NCK; ++u) {
             if constexpr (MB && !BB && !SPLIT) {
@@ -322,31 +365,9 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
         }
         __syncthreads();
 
-        // ---- phase 2: mode-1 contraction of this super-block on MFMA.
+        // ---- phase 2: mode-1 contraction of this block on MFMA.
         // Wave w owns stacked row tiles w, w + 4, ...; rows of tile t are
         // rows of Om1 (t < RT) or of Om1 A1 (RT <= t < 2 RT).
-        const int rows_sb = min(SBR, I1 - sb * SBR);
-        const int nkb = (rows_sb + KBR - 1) / KBR;
-        struct AF {
-            u4 h, l;     // bfloat16 products: Om1 (h), or Om1 A1 high / low; float32: h as f4 bits
-        };
-        // A fragments in operand order: one contiguous 1 KB read per wave and
-        // tile; padding rows and columns are stored zeros, and unused tiles
-        // (t >= NRT) read nothing (offset past the buffer range)
-        auto load_a = [&](int kb, AF* A) {
-            const int kbg = sb * (SBR / KBR) + kb;
-#pragma unroll
-            for (int u = 0; u < RPW; ++u) {
-                const int t = wave + 4 * u;
-                const bool half = t >= RT;
-                const int tl = t - (half ? RT : 0);
-                const unsigned off = (t < NRT) ? (unsigned)((tl * nkbf + kbg) * 64 + lane) * 16u : OOB_A;
-                const auto& rs = half ? rom1c : rom1;
-                A[u].h = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-                if constexpr (MB)
-                    A[u].l = half ? __builtin_amdgcn_raw_buffer_load_b128(rs, off + fbytes, 0, 0) : u4{0u, 0u, 0u, 0u};
-            }
-        };
         auto mfma_block = [&](int kb, const AF* A) {
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
@@ -383,21 +404,36 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
             }
         };
         // the fragments of the next K-block are loaded while the current one
-        // is multiplied (two named buffers: no dynamically indexed arrays)
-        AF A0[RPW], A1[RPW];
-        load_a(0, A0);
-        for (int kb = 0; kb < nkb; kb += 2) {
-            if (kb + 1 < nkb) load_a(kb + 1, A1);
-            mfma_block(kb, A0);
-            if (kb + 1 < nkb) {
-                if (kb + 2 < nkb) load_a(kb + 2, A0);
-                mfma_block(kb + 1, A1);
+        // is multiplied (two named buffers: no dynamically indexed arrays);
+        // whole blocks unrolled, the last rows in a loop
+        if (nkb == NKB) {
+#pragma unroll
+            for (int kb = 0; kb < NKB; kb += 2) {
+                mfma_block(kb, A0);
+                if (kb + 2 < NKB) load_a(kb + 2, A0);
+                if (kb + 1 < NKB) {
+                    mfma_block(kb + 1, A1);
+                    if (kb + 3 < NKB) load_a(kb + 3, A1);
+                }
+            }
+        } else {
+            for (int kb = 0; kb < nkb; kb += 2) {
+                mfma_block(kb, A0);
+                if (kb + 1 < nkb) {
+                    if (kb + 2 < nkb) load_a(kb + 2, A0);
+                    mfma_block(kb + 1, A1);
+                    if (kb + 3 < nkb) load_a(kb + 3, A1);
+                }
             }
         }
     }
     if (!do_sketch) return;
 
     // ---- mode-1 results to LDS: Ys[16 t + r][col]
+    float* Pt0 = (newv ? d.PV : d.PW) + (size_t)tile * l1 * l2;
+    float* Pt1 = d.PW + (size_t)tile * l1 * l2;
+    Mode2Ops<TC> m2;
+    mode2_load<TC>(m2, wave, lane, l2, I2, i20, ncol, NRT, RT, d.om2, d.om2t);
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < RPW; ++u) {
@@ -411,9 +447,7 @@ __device__ __forceinline__ void tile_task(const Desc* __restrict__ descs, const 
     __syncthreads();
 
     // ---- mode-2 contraction: P[a][b] = sum_k Ys[a][k] Om2x[b][i20 + k]
-    float* Pt0 = (newv ? d.PV : d.PW) + (size_t)tile * l1 * l2;
-    float* Pt1 = d.PW + (size_t)tile * l1 * l2;
-    mode2_partials<TC, YP>(Ys, wave, lane, NRT, RT, l1, l2, I2, i20, ncol, d.om2, d.om2t, Pt0, Pt1);
+    mode2_partials_all<TC, YP>(Ys, m2, wave, lane, NRT, RT, l1, l2, Pt0, Pt1);
 }
 
 }  // namespace rtg
