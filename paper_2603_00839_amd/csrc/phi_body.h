@@ -156,6 +156,49 @@ __device__ __forceinline__ void phi_tile(const PhiArgs& a, int tile, float* smem
         for (int kk = 0; kk < nk; ++kk) dma_slab(klo + kk, kk);     // nk <= J <= 3 = NBUF
     }
 
+    // Register staging: the slab of the next input channel is loaded into
+    // registers while the current one is processed (all loads of a slab are
+    // issued together).  The first channel's slab is requested before
+    // anything else of the tile, its coefficients behind it and not it behind
+    // them, and Toeplitz taps are scalar loads: the slab used to wait for two
+    // round trips to memory, 6,000 of the 20,000 clocks of a lone tile
+    // (256 x 250 x 64 with C, half-width 6: 27.6 -> 26.8 us; Golub-Kahan runs,
+    // two operator calls a step: 6.18 -> 6.01 ms).
+    constexpr int NLD = VEC ? 1 : (SR * SC + 255) / 256;
+    // SL_VEC: the slab in 16-byte chunks (the layout of the asynchronous
+    // loads), zeros past the buffer range
+    constexpr int NCHV = SC * CPC;
+    constexpr int NLD4 = (SL == SL_VEC) ? (NCHV + 255) / 256 : 1;
+    f4v pre4[NLD4];
+    auto load_slab4 = [&](int k) {
+#pragma unroll
+        for (int it = 0; it < NLD4; ++it) {
+            const int c = it * 256 + tid;
+            const int col = c / CPC, rc = c % CPC;
+            const int i1 = i10 - R + 4 * rc, i2 = i20 - R + col;
+            const bool ok = (c < NCHV) & (rc < SR / 4) & (i1 >= 0) & (i1 < I1) & (i2 >= 0) & (i2 < I2);
+            const unsigned off = ok ? (unsigned)(((size_t)k * plane + (size_t)i2 * I1 + i1) * 4) : 0x80000000u;
+            pre4[it] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+        }
+    };
+    const float* srcf = (const float*)a.src;
+    const bf16_t* srch = (const bf16_t*)a.src;
+    float pre[NLD];
+    auto load_slab = [&](int k) {
+#pragma unroll
+        for (int it = 0; it < NLD; ++it) {
+            // unconditional load from a clamped address, masked afterwards
+            const int e = tid + 256 * it;
+            const int row = e % SR, c = e / SR;
+            const int i1 = i10 - R + row, i2 = i20 - R + c;
+            const bool inb = e < SR * SC && i1 >= 0 && i1 < I1 && i2 >= 0 && i2 < I2;
+            const size_t off = (size_t)k * plane + (size_t)min(max(i2, 0), I2 - 1) * I1 + min(max(i1, 0), I1 - 1);
+            const float v = BF16IN ? bf2f(*gptr(srch + off)) : *gptr(srcf + off);
+            pre[it] = inb ? v : 0.f;
+        }
+    };
+    if constexpr (SL == SL_VEC) load_slab4(klo);
+    else if constexpr (SL == SL_SCALAR) load_slab(klo);
     // band coefficients of this tile, zero-padded to R taps and to rows of
     // WP (a multiple of 4) floats: the passes read them as 16-byte LDS
     // broadcasts, four taps a read, with no branches
@@ -195,8 +238,8 @@ __device__ __forceinline__ void phi_tile(const PhiArgs& a, int tile, float* smem
 #pragma unroll
         for (int t = 0; t < WP; ++t) {
             const int dd = t - R;
-            const float v1 = (t <= 2 * R && dd >= -r1 && dd <= r1) ? *gptr(a.taps + r1 + dd) : 0.f;
-            const float v2 = (t <= 2 * R && dd >= -r2 && dd <= r2) ? *gptr(a.taps + 2 * RMAX_SPATIAL + 1 + r2 + dd) : 0.f;
+            const float v1 = (t <= 2 * R && dd >= -r1 && dd <= r1) ? *cptr(a.taps + r1 + dd) : 0.f;
+            const float v2 = (t <= 2 * R && dd >= -r2 && dd <= r2) ? *cptr(a.taps + 2 * RMAX_SPATIAL + 1 + r2 + dd) : 0.f;
             tA1[t] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v1)));
             tA2[t] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v2)));
         }
@@ -212,44 +255,6 @@ __device__ __forceinline__ void phi_tile(const PhiArgs& a, int tile, float* smem
         }
     };
 
-    // Register staging: the slab of the next input channel is loaded into
-    // registers while the current one is processed (all loads of a slab are
-    // issued together).
-    constexpr int NLD = VEC ? 1 : (SR * SC + 255) / 256;
-    // SL_VEC: the slab in 16-byte chunks (the layout of the asynchronous
-    // loads), zeros past the buffer range
-    constexpr int NCHV = SC * CPC;
-    constexpr int NLD4 = (SL == SL_VEC) ? (NCHV + 255) / 256 : 1;
-    f4v pre4[NLD4];
-    auto load_slab4 = [&](int k) {
-#pragma unroll
-        for (int it = 0; it < NLD4; ++it) {
-            const int c = it * 256 + tid;
-            const int col = c / CPC, rc = c % CPC;
-            const int i1 = i10 - R + 4 * rc, i2 = i20 - R + col;
-            const bool ok = (c < NCHV) & (rc < SR / 4) & (i1 >= 0) & (i1 < I1) & (i2 >= 0) & (i2 < I2);
-            const unsigned off = ok ? (unsigned)(((size_t)k * plane + (size_t)i2 * I1 + i1) * 4) : 0x80000000u;
-            pre4[it] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
-        }
-    };
-    const float* srcf = (const float*)a.src;
-    const bf16_t* srch = (const bf16_t*)a.src;
-    float pre[NLD];
-    auto load_slab = [&](int k) {
-#pragma unroll
-        for (int it = 0; it < NLD; ++it) {
-            // unconditional load from a clamped address, masked afterwards
-            const int e = tid + 256 * it;
-            const int row = e % SR, c = e / SR;
-            const int i1 = i10 - R + row, i2 = i20 - R + c;
-            const bool inb = e < SR * SC && i1 >= 0 && i1 < I1 && i2 >= 0 && i2 < I2;
-            const size_t off = (size_t)k * plane + (size_t)min(max(i2, 0), I2 - 1) * I1 + min(max(i1, 0), I1 - 1);
-            const float v = BF16IN ? bf2f(*gptr(srch + off)) : *gptr(srcf + off);
-            pre[it] = inb ? v : 0.f;
-        }
-    };
-    if constexpr (SL == SL_VEC) load_slab4(klo);
-    else if constexpr (SL == SL_SCALAR) load_slab(klo);
     for (int kk = 0; kk < nk; ++kk) {
         const int k = klo + kk;
         float* S = Sall + (kk % NBUF) * SC * SRP;

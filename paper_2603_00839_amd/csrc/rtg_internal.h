@@ -166,6 +166,13 @@ __device__ __forceinline__ RTG_GLOBAL T* gptr_w(T* p) {
     return (RTG_GLOBAL T*)p;
 }
 
+// Operator and sketch data that no kernel writes, at a wave-uniform address:
+// scalar loads.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* cptr(const T* p) {
+    return (const __attribute__((address_space(4))) T*)p;
+}
+
 // The problem that holds tile b of a batch (the largest p with starts[p] <= b;
 // starts has count + 1 entries, starts[0] = 0) and the tile's index in it.
 // Called by whole waves with the same b in every lane: each lane looks at one
