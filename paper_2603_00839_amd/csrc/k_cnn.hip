@@ -19,7 +19,7 @@
 // pass the same kernel runs on flipped, transposed weights and masks the
 // result with the ReLU of the layer input.
 // Weight gradient: dW[co][tap, ci] = sum_pixels g[pixel][co] x[pixel + tap][ci]
-// on MFMA with K = pixels (both operands staged transposed in LDS), per-
+// on MFMA with K = pixels (both operands transposed on the way to LDS), per-
 // workgroup partials reduced in a fixed order (deterministic).
 #include "rtg_internal.h"
 
@@ -606,102 +606,233 @@ __global__ void __launch_bounds__(C2_THREADS) k_conv2(Conv2Args a) {
     }
 }
 
-template <int CIN_S, int COUT_S, int COUT_M>
-__global__ void __launch_bounds__(256) k_wgrad(WgradArgs a) {
-    constexpr int KPAD = kpad_of(CIN_S);
-    constexpr int TAPS = KPAD / CIN_S;    // 9, or 12 with zero padding
-    constexpr int NT = KPAD / 16, MT = COUT_M / 16;
-    constexpr int TILES = NT * MT;
-    constexpr int SLOTS = (TILES + 3) / 4;
-    constexpr int PX = 32, PXL = PX + 8;  // pixels per chunk, padded LDS row
-    __shared__ bf16_t gT[COUT_M * PXL];
-    __shared__ bf16_t xs[TAPS * CIN_S * PXL];
+// Weight gradient.  A workgroup takes a strip of WG_PX pixels along i1 and
+// a.rows rows of one image, four rows at a time: wave w stages gradient row w
+// and the input row below it (8 pixels x 8 channels a lane, transposed in
+// registers and written as 16-byte pieces of a channel's pixels), then adds
+// row w's products.  K = 16 pixels of v_mfma_f32_32x32x16_bf16; the nine taps
+// are three A operands (the gradient's pixels shifted by -1, 0, 1 in registers)
+// times three B operands (the input rows above, at and below), so an input row
+// is read and transposed once, not nine times.  With 8 stored channels the
+// three shifts (or rows) share one operand.  What bounds it: nothing alone;
+// staging, products and the partial sums' epilogue follow each other in
+// two workgroups per compute unit (32 images of 128 x 128, 32 to 32 channels:
+// 24.3 us, 0.40 PFLOP/s, from 90.7 us with every tap staged and scattered
+// to LDS two bytes at a time; 32 to 8 channels 16.7 us from 78).
+constexpr int WG_PX = 64;
+constexpr int WG_GST = WG_PX + 24;      // gradient row of a channel in LDS: 8 pixels to the left and right, 16-byte
+constexpr int WG_XST = WG_PX + 8;       // pieces in odd strides, so that 16 lanes' reads meet every bank once
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n16 = lane & 15, s = lane >> 4;
-    const int I1 = a.I1, I2 = a.I2;
-    const int ngrp = (I2 + a.rows - 1) / a.rows;
-    const int img = blockIdx.x / ngrp;
-    const int r0 = (blockIdx.x % ngrp) * a.rows;
-
-    for (int e = tid; e < COUT_M * PXL; e += 256) gT[e] = 0;
-    f4 acc[SLOTS];
+// 8 pixels (v[j]) x 8 channels (words of two) to 8 channels x 8 pixels
+__device__ __forceinline__ void transpose8(const u4 (&v)[8], u4 (&out)[8]) {
 #pragma unroll
-    for (int u = 0; u < SLOTS; ++u) acc[u] = f4{0.f, 0.f, 0.f, 0.f};
-    float dbacc = 0.f;
-
-    for (int i2 = r0; i2 < min(r0 + a.rows, I2); ++i2) {
-        for (int c0 = 0; c0 < I1; c0 += PX) {
-            __syncthreads();
-            // stage g^T: rows co < COUT_S (rows beyond stay zero)
-            for (int e = tid; e < PX * (COUT_S / 8); e += 256) {
-                const int px = e % PX, c8 = e / PX;
-                const int i1 = c0 + px;
-                const bool ok = i1 < I1;
-                const u4 v = *gptr((const u4*)(a.g + (((size_t)img * I2 + i2) * I1 + min(i1, I1 - 1)) * COUT_S + c8 * 8));
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    gT[(c8 * 8 + 2 * t) * PXL + px] = ok ? (bf16_t)(v[t] & 0xffffu) : (bf16_t)0;
-                    gT[(c8 * 8 + 2 * t + 1) * PXL + px] = ok ? (bf16_t)(v[t] >> 16) : (bf16_t)0;
-                }
-            }
-            // stage the shifted input for every tap: xs[tap][ci][px] = x[i1 + t1 - 1, i2 + t2 - 1][ci]
-            for (int e = tid; e < TAPS * PX * (CIN_S / 8); e += 256) {
-                const int px = e % PX;
-                const int r = e / PX;
-                const int c8 = r % (CIN_S / 8), tap = r / (CIN_S / 8);
-                const int y1 = c0 + px + tap / 3 - 1, y2 = i2 + tap % 3 - 1;
-                const bool ok = tap < 9 && c0 + px < I1 && y1 >= 0 && y1 < I1 && y2 >= 0 && y2 < I2;
-                const int c1 = min(max(y1, 0), I1 - 1), c2 = min(max(y2, 0), I2 - 1);
-                const u4 v = *gptr((const u4*)(a.x + (((size_t)img * I2 + c2) * I1 + c1) * CIN_S + c8 * 8));
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    xs[(tap * CIN_S + c8 * 8 + 2 * t) * PXL + px] = ok ? (bf16_t)(v[t] & 0xffffu) : (bf16_t)0;
-                    xs[(tap * CIN_S + c8 * 8 + 2 * t + 1) * PXL + px] = ok ? (bf16_t)(v[t] >> 16) : (bf16_t)0;
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < SLOTS; ++u) {
-                const int t = wave + 4 * u;
-                if (t < TILES) {
-                    const int mt = t / NT, nt = t % NT;
-                    const bf8 A = __builtin_bit_cast(bf8, *(const u4*)(gT + (16 * mt + n16) * PXL + 8 * s));
-                    const bf8 B = __builtin_bit_cast(bf8, *(const u4*)(xs + (16 * nt + n16) * PXL + 8 * s));
-                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc[u], 0, 0, 0);
-                }
-            }
-            if (tid < COUT_M) {
-                for (int px = 0; px < PX; ++px) dbacc += bf2f(gT[tid * PXL + px]);
-            }
+        for (int q = 0; q < 4; ++q) {
+            out[2 * k][q] = __builtin_amdgcn_perm(v[2 * q + 1][k], v[2 * q][k], 0x05040100u);
+            out[2 * k + 1][q] = __builtin_amdgcn_perm(v[2 * q + 1][k], v[2 * q][k], 0x07060302u);
         }
-    }
-    float* part = a.part + (size_t)blockIdx.x * (COUT_M * KPAD + COUT_M);
-#pragma unroll
-    for (int u = 0; u < SLOTS; ++u) {
-        const int t = wave + 4 * u;
-        if (t < TILES) {
-            const int mt = t / NT, nt = t % NT;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                *gptr_w(part + (size_t)(16 * mt + 4 * s + i) * KPAD + 16 * nt + n16) = acc[u][i];
-        }
-    }
-    if (tid < COUT_M) *gptr_w(part + COUT_M * KPAD + tid) = dbacc;
 }
 
-// out[e] = sum over parts in a fixed order (deterministic)
-__global__ void k_reduce_parts(const float* __restrict__ part, int nparts, int len, float* __restrict__ out) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= len) return;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int w = 0;
-    for (; w + 8 <= nparts; w += 8) {
+template <int CIN_S, int COUT_S, int COUT_M>
+__global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a) {
+    constexpr int KPAD = kpad_of(CIN_S);
+    constexpr int NA = COUT_S == 32 ? 3 : 1, NB = CIN_S == 32 ? 3 : 1;
+    static_assert((COUT_S == 32 || COUT_S == 8) && (CIN_S == 32 || CIN_S == 8), "stored channels");
+    constexpr int GH = 4 * COUT_S * WG_GST, XH = 6 * CIN_S * WG_XST;      // bfloat16 elements
+    constexpr int RST = 40;                                               // row stride of a wave's 32 x 32 sums
+    constexpr int REDF = 2 * 4 * 32 * RST;
+    constexpr int BYTES = (GH + XH) * 2 > REDF * 4 ? (GH + XH) * 2 : REDF * 4;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
+    __shared__ float dbs[4][64];
+    bf16_t* G = (bf16_t*)smem;           // [4 rows][COUT_S][WG_GST], pixel c0 + i at 8 + i
+    bf16_t* X = G + GH;                  // [6 rows][CIN_S][WG_XST]: row q of the strip (q = 0: r0 - 1) at q % 6
+    float* red = (float*)smem;           // epilogue: [2][4 waves][32][RST]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int I1 = a.I1, I2 = a.I2;
+    const int ngrp = (I2 + a.rows - 1) / a.rows, nstr = (I1 + WG_PX - 1) / WG_PX;
+    const int grp = blockIdx.x % ngrp, img = blockIdx.x / ngrp / nstr;
+    const int c0 = blockIdx.x / ngrp % nstr * WG_PX;
+    const int r0 = grp * a.rows, rend = min(r0 + a.rows, I2);
+    const bf16_t* gimg = a.g + (size_t)img * I2 * I1 * COUT_S;
+    const bf16_t* ximg = a.x + (size_t)img * I2 * I1 * CIN_S;
+
+    // staging: lanes 0..31 the gradient, 32..63 the input; 8 pixels from
+    // c0 + 8 sb of channels 8 sc ..
+    const bool isx = lane >= 32;
+    const int sb = lane & 7, sc = (lane >> 3) & 3;
+    const int nch = isx ? CIN_S : COUT_S;
+    const bool has = 8 * sc < nch;
+    const bf16_t* simg = (isx ? ximg : gimg) + (has ? 8 * sc : 0);
+    auto load8 = [&](int row, bool ok, u4 (&v)[8]) {
+        const int rc = min(max(row, 0), I2 - 1);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] += *gptr(part + (size_t)(w + u) * len + e);
+        for (int j = 0; j < 8; ++j) {
+            const int px = c0 + 8 * sb + j;
+            const u4 t = *gptr((const u4*)(simg + ((size_t)rc * I1 + min(px, I1 - 1)) * nch));
+            v[j] = ok && px < I1 ? t : u4{0u, 0u, 0u, 0u};
+        }
+    };
+    // the gradient's pixels c0 - 1 and c0 + WG_PX (8 lanes: side, 8 channels)
+    const int eside = lane & 1, ec = lane >> 1;
+    const bool eon = lane < 8 && 8 * ec < COUT_S;
+    auto load_edge = [&](int row, bool ok) {
+        const int px = eside ? c0 + WG_PX : c0 - 1;
+        u4 t{0u, 0u, 0u, 0u};
+        if (eon && ok && px >= 0 && px < I1) t = *gptr((const u4*)(gimg + ((size_t)row * I1 + px) * COUT_S + 8 * ec));
+        return t;
+    };
+    auto put8 = [&](const u4 (&v)[8], bf16_t* base, int stride) {       // base: channel 0, this lane's pixels
+        u4 t[8];
+        transpose8(v, t);
+        if (has) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) *(u4*)(base + (8 * sc + i) * stride) = t[i];
+        }
+    };
+
+    f16v acc[NA][NB];
+#pragma unroll
+    for (int ta = 0; ta < NA; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[ta][tb][i] = 0.f;
+    float db = 0.f;
+
+    const int l31 = lane & 31, half = lane >> 5;
+    const int niter = (rend - r0 + 3) / 4;
+    u4 v[8], ev;
+    auto load_iter = [&](int it) {
+        const int gr = r0 + 4 * it + wave, xr = gr + 1;
+        load8(isx ? xr : gr, isx ? xr < I2 : gr < rend, v);
+        ev = load_edge(gr, gr < rend);
+    };
+    // rows r0 - 1 and r0 of the input, by the input lanes of waves 0 and 1
+    if (wave < 2) {
+        const int xr = r0 - 1 + wave;
+        u4 v0[8];
+        load8(isx ? xr : 0, isx && xr >= 0, v0);
+        load_iter(0);
+        if (isx) put8(v0, X + wave * CIN_S * WG_XST + 8 * sb, WG_XST);
+    } else {
+        load_iter(0);
     }
-    for (; w < nparts; ++w) acc[0] += *gptr(part + (size_t)w * len + e);
-    out[e] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    for (int it = 0; it < niter; ++it) {
+        __syncthreads();                                     // the last four rows' reads are done
+        {
+            const int q = (4 * it + 2 + wave) % 6;
+            bf16_t* base = isx ? X + q * CIN_S * WG_XST + 8 * sb : G + wave * COUT_S * WG_GST + 8 + 8 * sb;
+            put8(v, base, isx ? WG_XST : WG_GST);
+            if (eon) {
+                bf16_t* e = G + (wave * COUT_S + 8 * ec) * WG_GST + (eside ? 8 + WG_PX : 7);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) e[i * WG_GST] = (bf16_t)(ev[i / 2] >> (16 * (i & 1)));
+            }
+        }
+        if (it + 1 < niter) load_iter(it + 1);
+        __syncthreads();
+        if (r0 + 4 * it + wave < rend) {
+            const bf16_t* gr = G + (wave * COUT_S + l31 % COUT_S) * WG_GST + 8 + 8 * half;
+            const bf16_t* xr[NB];
+#pragma unroll
+            for (int tb = 0; tb < NB; ++tb) {
+                const int t2 = NB == 3 ? tb : min(l31 / CIN_S, 2);
+                xr[tb] = X + ((4 * it + wave + t2) % 6 * CIN_S + l31 % CIN_S) * WG_XST + 8 * half;
+            }
+#pragma unroll
+            for (int ks = 0; ks < WG_PX / 16; ++ks) {
+                const u4 w = *(const u4*)(gr + 16 * ks);
+                const unsigned wl = *(const unsigned*)(gr + 16 * ks - 2), wr = *(const unsigned*)(gr + 16 * ks + 8);
+                u4 B[NB];
+#pragma unroll
+                for (int tb = 0; tb < NB; ++tb) B[tb] = *(const u4*)(xr[tb] + 16 * ks);
+                // the pixels one to the left (t1 = 2), the own (1) and one to the right (0)
+                const unsigned q0 = __builtin_amdgcn_alignbit(w[0], wl, 16), q1 = __builtin_amdgcn_alignbit(w[1], w[0], 16),
+                               q2 = __builtin_amdgcn_alignbit(w[2], w[1], 16), q3 = __builtin_amdgcn_alignbit(w[3], w[2], 16),
+                               q4 = __builtin_amdgcn_alignbit(wr, w[3], 16);
+                const u4 Ar{q1, q2, q3, q4}, Al{q0, q1, q2, q3};
+                u4 A[NA];
+                if constexpr (NA == 3) {
+                    A[0] = Ar; A[1] = w; A[2] = Al;
+                } else {
+                    const int t1 = l31 / COUT_S;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) A[0][i] = t1 == 0 ? Ar[i] : t1 == 1 ? w[i] : Al[i];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    db += __uint_as_float(w[i] << 16);
+                    db += __uint_as_float(w[i] & 0xffff0000u);
+                }
+#pragma unroll
+                for (int ta = 0; ta < NA; ++ta)
+#pragma unroll
+                    for (int tb = 0; tb < NB; ++tb)
+                        acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            __builtin_bit_cast(bf8, A[ta]), __builtin_bit_cast(bf8, B[tb]), acc[ta][tb], 0, 0, 0);
+            }
+        }
+    }
+
+    // the four waves' sums, one 32 x 32 tile after the other through LDS
+    float* part = a.part + (size_t)blockIdx.x * (COUT_M * KPAD + COUT_M);
+    dbs[wave][lane] = db;
+    __syncthreads();                                         // the rows in LDS are no longer read
+#pragma unroll
+    for (int ta = 0; ta < NA; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb) {
+            float* R = red + ((ta * NB + tb) & 1) * 4 * 32 * RST;
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                R[(wave * 32 + i % 4 + 8 * (i / 4) + 4 * half) * RST + l31] = acc[ta][tb][i];
+            __syncthreads();
+            const int m = tid >> 3, n = 4 * (tid & 7);
+            f4 s = *(const f4*)(R + m * RST + n);
+#pragma unroll
+            for (int w = 1; w < 4; ++w) s += *(const f4*)(R + (w * 32 + m) * RST + n);
+            const int t1 = (32 * ta + m) / COUT_S, co = (32 * ta + m) % COUT_S;
+            const int t2 = (32 * tb + n) / CIN_S, ci = (32 * tb + n) % CIN_S;
+            if (t1 < 3 && t2 < 3) *gptr_w((f4*)(part + (size_t)co * KPAD + (t1 * 3 + t2) * CIN_S + ci)) = s;
+        }
+    // the padding of the weights: zero
+    for (int e = tid; e < COUT_M * KPAD; e += 256)
+        if (e / KPAD >= COUT_S || e % KPAD >= 9 * CIN_S) *gptr_w(part + e) = 0.f;
+    if (tid < COUT_M) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) s += dbs[w][tid] + dbs[w][32 + tid];
+        *gptr_w(part + COUT_M * KPAD + tid) = tid < COUT_S ? s : 0.f;
+    }
+}
+
+// out[e] = sum over parts in a fixed order (deterministic).  E elements per
+// workgroup, 256 / E lanes for each element's parts: with one lane per element
+// the parts were a chain of loads in 37 workgroups (512 parts of 9,248
+// elements: 21.8 us, now 4.8).
+template <int E>
+__global__ void __launch_bounds__(256) k_reduce_parts(const float* __restrict__ part, int nparts, int len,
+                                                      float* __restrict__ out) {
+    constexpr int L = 256 / E;
+    __shared__ float sums[L][E];
+    const int e = threadIdx.x % E, l = threadIdx.x / E;
+    const int at = blockIdx.x * E + e, atc = min(at, len - 1);
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    int w = l;
+    for (; w + 7 * L < nparts; w += 8 * L) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc[u] += *gptr(part + (size_t)(w + u * L) * len + atc);
+    }
+    for (; w < nparts; w += L) acc[0] += *gptr(part + (size_t)w * len + atc);
+    sums[l][e] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    for (int h = L / 2; h > 0; h /= 2) {
+        __syncthreads();
+        if (l < h) sums[l][e] += sums[l + h][e];
+    }
+    if (l == 0 && at < len) out[at] = sums[0][e];
 }
 
 // planar float32 [N][3][I2][I1] -> NHWC bfloat16 with 8 stored channels
@@ -805,11 +936,19 @@ StateLayout state_layout() {
     return S;
 }
 
-constexpr int WG_ROWS = 8;
+// rows per workgroup of the weight gradient: four at a time, as many of these
+// steps as leave about two workgroups per compute unit (each ends with a
+// partial sum of every weight)
+constexpr int WG_MAX = 2 * 256;
+
+int wgrad_rows(int N, int I1, int I2) {
+    const long long strips = (long long)N * ((I1 + WG_PX - 1) / WG_PX), steps = (I2 + 3) / 4;
+    return 4 * (int)std::min(steps, (strips * steps + WG_MAX - 1) / WG_MAX);
+}
 
 struct WsLayout {
     size_t xin, act[NL - 1], g8, gA, gB, part, loss, total;
-    int nconv, nwg;
+    int nconv, nwg, wg_rows;
 };
 
 WsLayout ws_layout(int N, int I1, int I2) {
@@ -823,7 +962,8 @@ WsLayout ws_layout(int N, int I1, int I2) {
     W.gA = take(px * 32 * 2);
     W.gB = take(px * 32 * 2);
     W.nconv = std::min(N * ((I2 + CONV_TH - 1) / CONV_TH) * ((I1 + 63) / 64), CONV_MAX_WG);
-    W.nwg = N * ((I2 + WG_ROWS - 1) / WG_ROWS);
+    W.wg_rows = wgrad_rows(N, I1, I2);
+    W.nwg = N * ((I1 + WG_PX - 1) / WG_PX) * ((I2 + W.wg_rows - 1) / W.wg_rows);
     W.part = take((size_t)W.nwg * (32 * kpad_of(32) + 32) * 4);
     W.loss = take((size_t)W.nconv * 4 + 4);
     W.total = al(off);
@@ -1009,19 +1149,19 @@ int rtg_cnn_gradients(void* state, const float* C, const float* Y, int N, int I1
         if (l < NL - 1) acts[l + 1] = out;
     }
     // loss = mean squared error (sum of per-workgroup partials / elements)
-    hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(64), 0, s, (const float*)(w + W.loss), W.nconv, 1, loss);
+    hipLaunchKernelGGL(k_reduce_parts<1>, dim3(1), dim3(256), 0, s, (const float*)(w + W.loss), W.nconv, 1, loss);
     // backward
     const bf16_t* g = (const bf16_t*)(w + W.g8);
     for (int l = NL - 1; l >= 0; --l) {
         const LayerOff& o = S.L[l];
-        WgradArgs wa{N, I1, I2, WG_ROWS, g, acts[l], (float*)(w + W.part)};
+        WgradArgs wa{N, I1, I2, W.wg_rows, g, acts[l], (float*)(w + W.part)};
         hipError_t e;
         if (l == 0) e = wgrad<8, 32, 32>(wa, W.nwg, s);
         else if (l < NL - 1) e = wgrad<32, 32, 32>(wa, W.nwg, s);
         else e = wgrad<32, 8, 16>(wa, W.nwg, s);
         if (e != hipSuccess) return RTG_E_HIP;
         const int len = o.nw + o.nb;
-        hipLaunchKernelGGL(k_reduce_parts, dim3((len + 255) / 256), dim3(256), 0, s, (const float*)(w + W.part),
+        hipLaunchKernelGGL(k_reduce_parts<32>, dim3((len + 31) / 32), dim3(256), 0, s, (const float*)(w + W.part),
                            W.nwg, len, (float*)(st + o.gW));
         if (l > 0) {
             // gradient w.r.t. the layer input, masked by the ReLU of that input

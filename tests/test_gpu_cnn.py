@@ -182,3 +182,37 @@ def test_adam_four_steps_match_reference():
     for l in range(6):
         for k in ("w", "b"):
             np.testing.assert_allclose(after[l][k], ref[l][k], rtol=1e-5, atol=1e-7)
+
+
+# N, I1, I2: strips of 64 pixels (one, a remainder, several), rows in fours
+# (fewer than four, remainders), workgroups of several steps of four rows
+@pytest.mark.parametrize("shape", [(1, 8, 3), (1, 64, 4), (2, 72, 5), (1, 136, 9), (3, 24, 37), (40, 72, 34)], ids=str)
+def test_weight_gradient_over_its_tiles(shape):
+    import torch
+    from paper_2603_00839_amd import rtg
+    banner(f"cnn weight gradient {shape}")
+    N, I1, I2 = shape
+    params = random_params(14, last_scale=1.0)
+    net = rtg.WarmStartNet(flat(params))
+    pq = unflat(U.bf16_round(flat(params)))
+    # the first and the last image differ, the others repeat the first
+    C = np.repeat(images(15, 1, I1, I2), N, axis=0)
+    C[-1] = images(16, 1, I1, I2)[0]
+    Y = C + 0.1
+    net.gradients(torch.from_numpy(C).cuda(), torch.from_numpy(Y).cuda())
+    got = unflat(net.read_gradients())
+    want = [{k: np.zeros_like(v, dtype=np.float64) for k, v in p.items()} for p in got]
+    for n, weight in ((0, (N - 1) / N), (N - 1, 1 / N)):
+        c = to_oracle(C[n])
+        cq = U.bf16_round(c).reshape(c.shape)
+        x0, acts = cnn.forward(pq, cq)
+        acts[0] = cq
+        acts[-1] = x0 - cq + c - cq
+        for w, g in zip(want, cnn.backward(pq, acts, to_oracle(Y[n]))):
+            for k in w:
+                w[k] += weight * g[k]
+    for l in range(6):
+        for k in ("w", "b"):
+            r = U.rel(got[l][k], want[l][k])
+            print(f"layer {l} {k}: rel {r:.3e}", file=sys.stderr)
+            assert r < 5e-2, (l, k, r)
