@@ -62,8 +62,13 @@ constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
 template <int R, bool TP, bool MB>
 struct PersistLds {
+    // Rows per block of the tile stage: at 128 the mixed form spills 98
+    // registers beside the operator's and the Gram step's (256 uneven problems:
+    // 95.8 ms per batch, 81.0 at 64); the float32 form does not (86.3 ms at
+    // 128, 87.8 at 64).
+    static constexpr int SBR = MB ? 64 : 128;
     static constexpr int PHI = PhiLayout<R, 4, SL_VEC>::FLOATS * 4;
-    static constexpr int TILE = cmax((int)sizeof(TileShared<MB, false, 4, 128>), (int)sizeof(TileShared<MB, MB, 4, 128>));
+    static constexpr int TILE = cmax((int)sizeof(TileShared<MB, false, 4, SBR>), (int)sizeof(TileShared<MB, MB, 4, SBR>));
     static constexpr int BYTES = cmax(cmax(PHI, TILE), (int)sizeof(GramSmem));
 };
 
@@ -248,14 +253,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
             phi_batched_task<R, false, 4, false, SL_VEC, TP>(descs, starts, a.count, k.mode, k.arg, k.b,
                                                              (float*)lds);
         } else if (k.kind == KIND_TILE) {
+            constexpr int SBR = PersistLds<R, TP, MB>::SBR;
             // a float32 source in the mixed form is split into two bfloat16
             // planes (R0); new basis tensors take one plane
             if (MB && k.mode == TM_SKETCH_SRC)
-                tile_task<false, MB, MB, 4, 128>(descs, starts, a.count, k.mode, 0, 0, 0, k.b,
-                                            *(TileShared<MB, MB, 4, 128>*)lds);
+                tile_task<false, MB, MB, 4, SBR>(descs, starts, a.count, k.mode, 0, 0, 0, k.b,
+                                            *(TileShared<MB, MB, 4, SBR>*)lds);
             else
-                tile_task<false, MB, false, 4, 128>(descs, starts, a.count, k.mode, k.arg, k.arg, 0, k.b,
-                                               *(TileShared<MB, false, 4, 128>*)lds);
+                tile_task<false, MB, false, 4, SBR>(descs, starts, a.count, k.mode, k.arg, k.arg, 0, k.b,
+                                               *(TileShared<MB, false, 4, SBR>*)lds);
         } else {
             gram_task<false>(descs, starts, a.count, k.mode, k.arg, nullptr, k.b, *(GramSmem*)lds);
         }
