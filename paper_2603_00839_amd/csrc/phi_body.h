@@ -158,7 +158,7 @@ __device__ __forceinline__ void phi_tile(const PhiArgs& a, int tile, float* smem
 
     // Register staging: the slab of the next input channel is loaded into
     // registers while the current one is processed (all loads of a slab are
-    // issued together).  The first channel's slab is requested before
+    // issued together).  A 16-byte slab of the first channel is requested before
     // anything else of the tile, its coefficients behind it and not it behind
     // them, and Toeplitz taps are scalar loads: the slab used to wait for two
     // round trips to memory, 6,000 of the 20,000 clocks of a lone tile
@@ -198,7 +198,6 @@ __device__ __forceinline__ void phi_tile(const PhiArgs& a, int tile, float* smem
         }
     };
     if constexpr (SL == SL_VEC) load_slab4(klo);
-    else if constexpr (SL == SL_SCALAR) load_slab(klo);
     // band coefficients of this tile, zero-padded to R taps and to rows of
     // WP (a multiple of 4) floats: the passes read them as 16-byte LDS
     // broadcasts, four taps a read, with no branches
@@ -255,6 +254,10 @@ __device__ __forceinline__ void phi_tile(const PhiArgs& a, int tile, float* smem
         }
     };
 
+    // a slab of single words after the coefficients: its 15 to 20 loads a lane
+    // in front of them cost the bfloat16 stencil 10 % (120x102x3, half-width 6:
+    // 26.0 us, 23.5 here)
+    if constexpr (SL == SL_SCALAR) load_slab(klo);
     for (int kk = 0; kk < nk; ++kk) {
         const int k = klo + kk;
         float* S = Sall + (kk % NBUF) * SC * SRP;
