@@ -25,12 +25,17 @@ namespace rtg {
 
 // A pair of columns counts as orthogonal once |a_p . a_q| <= tol ||a_p|| ||a_q||;
 // below about n * eps the inner product is rounding noise and rotations stop
-// making progress.  A sweep that met no cosine above JACOBI_LAST ends the
-// process without another one to confirm it: convergence is quadratic, and
-// with the single-precision angle used here a rotation leaves at most 1e-7 of
-// the cosine it met, so the largest one left is below tol.
+// making progress.  The process ends after a sweep that rotated nothing, or
+// after one whose rotations were all so small that the next would find nothing
+// to rotate.  A rotation of (p, q) by the angle t adds t ||a_q|| / ||a_p|| times
+// cos(q, r) to cos(p, r), and t ||a_q|| / ||a_p|| is at most
+//   u = |cos(p, q)| max(||a_p||^2, ||a_q||^2) / | ||a_p||^2 - ||a_q||^2 |,
+// which is no smaller than the cosine itself: columns of close norms turn by
+// large angles at tiny cosines and put back what was rotated away before.  With
+// every u of a sweep below 2e-8, the 2 (k - 2) <= 188 rotations that a pair meets
+// after its own leave at most 188 (2e-8)^2 = 7.5e-14 of it.
 constexpr double JACOBI_TOL2 = 1e-26;    // (1e-13)^2
-constexpr double JACOBI_LAST2 = 1e-15;   // (3e-8)^2
+constexpr double JACOBI_LAST2 = 4e-16;   // (2e-8)^2
 
 // Sum over a group of 8 lanes, in every lane (VALU cross-lane moves, no LDS
 // round trip): neighbours, then pairs within a quad, then the mirrored quad.
@@ -46,6 +51,13 @@ __device__ __forceinline__ double sum8(double v) {
     v += dpp_f64<0x4E>(v);     // quad_perm [2, 3, 0, 1]
     v += dpp_f64<0x141>(v);    // row_half_mirror
     return v;
+}
+
+// 1 / sqrt(x) for x in [1/4, 2]: the hardware's estimate and two Newton steps
+__device__ __forceinline__ double rsqrt_f64(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(y * 0.5, fma(-x * y, y, 1.0), y);
+    return fma(y * 0.5, fma(-x * y, y, 1.0), y);
 }
 
 __device__ __forceinline__ double wave_max(double v) {
@@ -68,14 +80,14 @@ __device__ __forceinline__ double proj_res2(const double* sig, const double* gh,
 // A chain of (sweeps) x (k - 1) rounds, each a barrier: the length of a round
 // is what the kernel takes.  The rotations work on R^T with g_R as one more
 // row, so no matrix W is accumulated (half the LDS traffic of a round); the
-// dot products are reduced by cross-lane moves instead of through LDS; the
-// rotation's angle is taken in single precision (it only steers convergence:
-// cosine and sine are normalised in float64, so the rotations are orthogonal
-// to rounding).  Eight lanes per pair: a problem of k = 50 then has one wave
+// dot products are reduced by cross-lane moves instead of through LDS; cosine
+// and sine come from two reciprocal square roots by the half-angle formulas,
+// without a division.  Eight lanes per pair: a problem of k = 50 then has one wave
 // per SIMD.  With sixteen it had two, and a round was bound by their float64
-// issue (1,750 clocks against 1,520).  NR: rows per lane, k <= 8 NR (a runtime
-// row count cost a scalar branch per row).  One problem, k = 50: 920 -> 350 us;
-// k = 20: 176 -> 75 us.
+// issue (1,750 clocks against 1,520, both with the angle in single precision,
+// which saves 3 % of the kernel).  NR: rows per lane, k <= 8 NR (a runtime row
+// count cost a scalar branch per row).  One problem, k = 50: 920 -> 347 us;
+// k = 20: 178 -> 87 us.
 template <int NR>
 __global__ void __launch_bounds__(384) k_solve(const Desc* __restrict__ descs) {
     // A lane holds the row pairs 2 gl, 2 gl + 1 (mod 16): 16-byte LDS accesses.
@@ -86,7 +98,7 @@ __global__ void __launch_bounds__(384) k_solve(const Desc* __restrict__ descs) {
     typedef double d2 __attribute__((ext_vector_type(2)));
     __shared__ __attribute__((aligned(16))) double As[8 * NR * LD];
     __shared__ double sig[MMAX], gh[MMAX], fco[MMAX];
-    __shared__ int s_big[3];                      // per sweep: a cosine above JACOBI_LAST was met
+    __shared__ int s_big[3];                      // per sweep: a rotation's u was above JACOBI_LAST
     __shared__ int s_cnt[2][8];                  // per wave: its points below the target (two passes in turn)
     __shared__ double s_mu;
     __shared__ int s_flags;
@@ -162,22 +174,19 @@ __global__ void __launch_bounds__(384) k_solve(const Desc* __restrict__ descs) {
                 ga = sum8(ga);
                 const double g2 = ga * ga, ab = al * be;
                 if (g2 > JACOBI_TOL2 * ab) {
-                    big = big || g2 > JACOBI_LAST2 * ab;
-                    // t = tan of the angle: sign(z) / (|z| + sqrt(1 + z^2)), z = (be - al) / (2 ga)
+                    // angle t: cos 2t = |df| / hyp, sin 2t = 2 ga / hyp, hyp = sqrt(df^2 + (2 ga)^2)
                     const double df = be - al, g2x = 2.0 * ga;
-                    // (both scaled to about 1 first, so that their single-precision
-                    // values do not overflow or vanish together)
+                    // (both scaled to about 1 first, so that their squares do
+                    // not overflow or vanish together)
                     const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(df), fabs(g2x)));
-                    const float dff = (float)__builtin_ldexp(df, ex), gf = (float)__builtin_ldexp(g2x, ex);
-                    const float rt = __builtin_amdgcn_sqrtf(fmaf(dff, dff, gf * gf));
-                    const float tf = gf * __builtin_amdgcn_rcpf(fabsf(dff) + rt);
-                    const double t = (double)(dff < 0.f ? -tf : tf);
-                    const double q1 = fma(t, t, 1.0);
-                    // 1 / sqrt(q1), 1 <= q1 <= 2: the hardware's estimate and two Newton steps
-                    double cth = __builtin_amdgcn_rsq(q1);
-                    cth = fma(cth * 0.5, fma(-q1 * cth, cth, 1.0), cth);
-                    cth = fma(cth * 0.5, fma(-q1 * cth, cth, 1.0), cth);
-                    const double sth = cth * t;
+                    const double dfs = __builtin_ldexp(df, ex), gs = __builtin_ldexp(g2x, ex);
+                    const double mx = __builtin_ldexp(fmax(al, be), ex);
+                    big = big || g2 * (mx * mx) > JACOBI_LAST2 * ab * (dfs * dfs);
+                    const double ih = rsqrt_f64(fma(dfs, dfs, gs * gs));      // 1 / hyp
+                    const double c2 = fma(0.5 * fabs(dfs), ih, 0.5);          // cos^2 t, in [1/2, 1]
+                    const double ic = rsqrt_f64(c2);
+                    const double cth = c2 * ic;
+                    const double sth = (df < 0.0 ? -0.5 : 0.5) * gs * ih * ic;
 #pragma unroll
                     for (int q = 0; q < NR; q += 2) {
                         ca[4 * q] = d2{fma(cth, x[q], -sth * y[q]), fma(cth, x[q + 1], -sth * y[q + 1])};

@@ -14,7 +14,7 @@ import numpy as np
 import pytest
 
 from paper_2603_00839_amd import synth
-from oracle.projected import projected_tikhonov
+from oracle.projected import projected_tikhonov, solve_14
 import _util as U
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +49,52 @@ def test_projected_solve_matches_float64(m, rule):
     np.testing.assert_allclose(info.mu, ref["mu"], rtol=1e-6)
     np.testing.assert_allclose(info.res_proj, ref["res_proj"], rtol=1e-7)
     assert err <= (m + 1) * 2.0 ** -24 * scale
+
+
+@pytest.mark.parametrize("m", [10, 40, 96])
+@pytest.mark.parametrize("bits", [26, 24, 20])
+def test_projected_solve_with_clustered_singular_values(m, bits):
+    """Singular values within a few eps = 2^-bits of 1, where the SVD's
+    rotations turn by large angles at cosines of eps and put back what earlier
+    ones rotated away.  Phi shifts an image by one pixel and adds eps times the
+    pixel and its other neighbour; from a single pixel and with Frobenius
+    products every tensor and product is exact, and H is tridiagonal with ones
+    below the diagonal and eps on and above it.
+
+    y is read where the solve leaves it, in the caller's workspace (the only
+    256-byte aligned run of float64 values close to the reference's), since X
+    takes it rounded to float32.  Columns orthogonal to 1e-13 in every pair
+    leave a relative error of at most (k - 1) 1e-13 s_max^2 / (s_min^2 + mu)
+    in y; the bar is twice that for the roundings of the rotations."""
+    import torch
+    from paper_2603_00839_amd import rtg
+    I1, I2, J, eps = 104, 40, 3, 2.0 ** -bits
+
+    def band(n, taps):
+        b = np.repeat(np.array([taps], np.float32), n, axis=0)
+        b[0, 0] = b[-1, 2] = 0.0
+        return b
+
+    one = (0.0, 1.0, 0.0)
+    op = rtg.setup_operator(I1, I2, J, band(I1, (1.0, eps, eps)), band(I2, one), band(J, one))
+    sk = rtg.setup_sketch(I1, I2, J, None, None, None)
+    C = np.zeros((I1, I2, J), np.float32)
+    C[0, 5, 1] = 1.0
+    Cd = U.to_dev(C)
+    H = rtg.arnoldi(op, sk, Cd, m, bd_tol=0.0)["H"].cpu().numpy()
+    want = np.eye(m + 1, m, k=-1) + eps * (np.eye(m + 1, m) + np.eye(m + 1, m, k=1))
+    np.testing.assert_allclose(H, want, rtol=1e-15 + 4 * eps ** 2)    # (float32 sums of squares: 1 + eps^2)
+    mu = 0.25
+    # (the normal equations: H^T e_1 is of size eps and exact, unlike the SVD's U^T e_1)
+    ref = solve_14(H, 1.0, mu)
+    ws = torch.zeros(rtg.workspace_bytes(op, sk, m), dtype=torch.uint8, device="cuda")
+    rtg.solve(op, sk, Cd, None, rtg.make_params(m, rtg.F32, mu=mu, bd_tol=0.0), ws=ws)
+    words = ws[:ws.numel() // 256 * 256].view(torch.float64).cpu().numpy()
+    rows = np.lib.stride_tricks.sliding_window_view(words, m)[::32]
+    with np.errstate(all="ignore"):
+        err = np.linalg.norm(rows - ref, axis=1) / np.linalg.norm(ref)
+    err = np.sort(np.where(np.isfinite(err), err, np.inf))
+    s = np.linalg.svd(H, compute_uv=False)
+    print(f"m {m} eps 2^-{bits}: y err {err[0]:.2e} (next {err[1]:.1e})", file=sys.stderr, flush=True)
+    assert err[1] > 1e-3
+    assert err[0] <= 2 * (m - 1) * 1e-13 * s[0] ** 2 / (s[-1] ** 2 + mu)
