@@ -941,14 +941,26 @@ StateLayout state_layout() {
 // partial sum of every weight)
 constexpr int WG_MAX = 2 * 256;
 
-int wgrad_rows(int N, int I1, int I2) {
+struct WgradPlan {
+    int rows, nwg;
+    long long nwg_max;
+};
+WgradPlan wgrad_plan(int N, int I1, int I2) {
     const long long strips = (long long)N * ((I1 + WG_PX - 1) / WG_PX), steps = (I2 + 3) / 4;
-    return 4 * (int)std::min(steps, (strips * steps + WG_MAX - 1) / WG_MAX);
+    WgradPlan P;
+    P.rows = 4 * (int)std::min(steps, (strips * steps + WG_MAX - 1) / WG_MAX);
+    P.nwg = (int)(strips * ((I2 + P.rows - 1) / P.rows));
+    // nwg falls where the rows of a workgroup go up by a step, so the workspace
+    // holds this bound of it, which grows with N, I1 and I2: a workspace of the
+    // largest images and batch then holds every smaller one
+    P.nwg_max = std::min(strips * steps, strips + WG_MAX);
+    return P;
 }
 
 struct WsLayout {
     size_t xin, act[NL - 1], g8, gA, gB, part, loss, total;
-    int nconv, nwg, wg_rows;
+    int nconv;
+    WgradPlan wg;
 };
 
 WsLayout ws_layout(int N, int I1, int I2) {
@@ -962,9 +974,8 @@ WsLayout ws_layout(int N, int I1, int I2) {
     W.gA = take(px * 32 * 2);
     W.gB = take(px * 32 * 2);
     W.nconv = std::min(N * ((I2 + CONV_TH - 1) / CONV_TH) * ((I1 + 63) / 64), CONV_MAX_WG);
-    W.wg_rows = wgrad_rows(N, I1, I2);
-    W.nwg = N * ((I1 + WG_PX - 1) / WG_PX) * ((I2 + W.wg_rows - 1) / W.wg_rows);
-    W.part = take((size_t)W.nwg * (32 * kpad_of(32) + 32) * 4);
+    W.wg = wgrad_plan(N, I1, I2);
+    W.part = take((size_t)W.wg.nwg_max * (32 * kpad_of(32) + 32) * 4);
     W.loss = take((size_t)W.nconv * 4 + 4);
     W.total = al(off);
     return W;
@@ -1154,15 +1165,15 @@ int rtg_cnn_gradients(void* state, const float* C, const float* Y, int N, int I1
     const bf16_t* g = (const bf16_t*)(w + W.g8);
     for (int l = NL - 1; l >= 0; --l) {
         const LayerOff& o = S.L[l];
-        WgradArgs wa{N, I1, I2, W.wg_rows, g, acts[l], (float*)(w + W.part)};
+        WgradArgs wa{N, I1, I2, W.wg.rows, g, acts[l], (float*)(w + W.part)};
         hipError_t e;
-        if (l == 0) e = wgrad<8, 32, 32>(wa, W.nwg, s);
-        else if (l < NL - 1) e = wgrad<32, 32, 32>(wa, W.nwg, s);
-        else e = wgrad<32, 8, 16>(wa, W.nwg, s);
+        if (l == 0) e = wgrad<8, 32, 32>(wa, W.wg.nwg, s);
+        else if (l < NL - 1) e = wgrad<32, 32, 32>(wa, W.wg.nwg, s);
+        else e = wgrad<32, 8, 16>(wa, W.wg.nwg, s);
         if (e != hipSuccess) return RTG_E_HIP;
         const int len = o.nw + o.nb;
         hipLaunchKernelGGL(k_reduce_parts<32>, dim3((len + 31) / 32), dim3(256), 0, s, (const float*)(w + W.part),
-                           W.nwg, len, (float*)(st + o.gW));
+                           W.wg.nwg, len, (float*)(st + o.gW));
         if (l > 0) {
             // gradient w.r.t. the layer input, masked by the ReLU of that input
             ConvArgs a{};
