@@ -79,8 +79,10 @@ long long col_tiles(const rtg_op_s* op) { return (long long)op->J * ((op->I2 + T
 // own partial sketches, which the Gram kernel reads back, so more parts cost
 // more than idle units do: one 512x512x3 problem (48 column tiles, m = 50)
 // takes 3.65 ms with whole columns, 3.03 with halves, 3.11 with quarters and
-// 3.5 with eighths; eight problems (384 tiles, general PSF, m = 40) 7.4 ms with
-// whole columns and 7.5 with halves.
+// 3.5 with eighths.  Halves against whole columns (m = 20, 512 rows, sketches of
+// 64 and of 128 squared, separable blur, general PSF and Golub-Kahan): 1.08 to
+// 1.13 times as fast at 96 column tiles, 0.84 to 1.00 times at 144, 0.92 to 0.96
+// at 384; columns of up to 256 rows 0.97 to 1.07 times at 6 to 120 tiles.
 constexpr long long PART_TILES = 128;
 int part_rows(const rtg_op_s* op, long long total) {
     const int blocks = (op->I1 + 63) / 64;
@@ -88,6 +90,17 @@ int part_rows(const rtg_op_s* op, long long total) {
 }
 int whole_rows(const rtg_op_s* op) { return (op->I1 + 63) / 64 * 64; }
 
+// Partial sketches that a problem's workspace holds: those of the halves where
+// any batch with this problem would take them, and no fewer for a problem with
+// more column tiles, so that the size depends on the problem alone and grows
+// with it (a workspace of the largest batch holds every smaller one).
+long long max_parts(const rtg_op_s* op, int bf16) {
+    const long long tiles = col_tiles(op);
+    if (bf16 || op->I1 <= 64) return tiles;
+    return std::max(tiles, 2 * std::min(tiles, PART_TILES));
+}
+
+// total: column tiles of the whole batch (0: whole columns)
 Layout problem_layout(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, long long total) {
     Layout L{};
     const size_t n = (size_t)op->I1 * op->I2 * op->J;
@@ -102,7 +115,7 @@ Layout problem_layout(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, l
     L.ntile_phi = phi_tiles(op->I1, op->I2, op->J, phi_jt(op->J));
     // an identity sketch keeps no partials, stored sketches or composed matrices
     const bool sk_bufs = !sk->identity;
-    const size_t part = sk_bufs ? (size_t)L.ntile_tile * sk->l1 * sk->l2 * sizeof(float) : 0;
+    const size_t part = sk_bufs ? (size_t)max_parts(op, bf16) * sk->l1 * sk->l2 * sizeof(float) : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) { off = align_up(off); size_t at = off; off += bytes; return at; };
     L.V = take((size_t)(m + 1) * n * es);
@@ -178,8 +191,8 @@ void fill_gk_sides(Desc& d, Desc& u, const rtg_op_s* op, const rtg_sk_s* sk, int
     u.SVx = d.SV;
 }
 
-size_t problem_bytes(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, int method, long long total) {
-    size_t b = problem_layout(op, sk, m, bf16, total).total;
+size_t problem_bytes(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, int method) {
+    size_t b = problem_layout(op, sk, m, bf16, 0).total;
     if (method == RTG_METHOD_GOLUB_KAHAN) b += gk_extra_layout(op, sk, m, bf16).total;
     return b;
 }
@@ -1117,14 +1130,14 @@ int rtg_sketch_noalloc(rtg_sk sk, int x_dtype, const void* X, float* SX, void* s
 size_t rtg_workspace_bytes(rtg_op op, rtg_sk sk, int m, int basis_dtype) {
     if (check_pair(op, sk) || check_m(sk, m)) return 0;
     // (room for the restart-cycle descriptor copy of rtg_solve with restarts)
-    return plan_bytes(1, 1, true) + problem_layout(op, sk, m, basis_dtype == RTG_BF16, col_tiles(op)).total;
+    return plan_bytes(1, 1, true) + problem_layout(op, sk, m, basis_dtype == RTG_BF16, 0).total;
 }
 
 int rtg_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t* v_offset, size_t* sv_offset) {
     int rc = check_pair(op, sk);
     if (rc) return rc;
     if ((rc = check_m(sk, m))) return rc;
-    Layout L = problem_layout(op, sk, m, basis_dtype == RTG_BF16, col_tiles(op));
+    Layout L = problem_layout(op, sk, m, basis_dtype == RTG_BF16, 0);
     if (v_offset) *v_offset = plan_bytes(1) + L.V;
     if (sv_offset) *sv_offset = plan_bytes(1) + L.SV;
     return RTG_OK;
@@ -1164,23 +1177,18 @@ size_t rtg_batch_workspace_bytes(int count, const rtg_problem* probs) {
     bool restart = false;
     for (int p = 0; p < count; ++p) restart = restart || probs[p].params.restarts > 0;
     size_t total = plan_bytes(count, method == RTG_METHOD_GOLUB_KAHAN ? 2 : 1, restart);
-    long long tiles = 0;
     for (int p = 0; p < count; ++p) {
         const rtg_problem& q = probs[p];
         if (check_pair(q.op, q.sk) || check_m(q.sk, q.params.m)) return 0;
         if (q.params.method != method) return 0;
-        tiles += col_tiles(q.op);
-    }
-    for (int p = 0; p < count; ++p) {
-        const rtg_problem& q = probs[p];
-        total += problem_bytes(q.op, q.sk, q.params.m, q.params.basis_dtype == RTG_BF16, method, tiles);
+        total += problem_bytes(q.op, q.sk, q.params.m, q.params.basis_dtype == RTG_BF16, method);
     }
     return total;
 }
 
 size_t rtg_gk_workspace_bytes(rtg_op op, rtg_sk sk, int m, int basis_dtype) {
     if (check_pair(op, sk) || check_m(sk, m)) return 0;
-    return plan_bytes(1, 2) + problem_bytes(op, sk, m, basis_dtype == RTG_BF16, RTG_METHOD_GOLUB_KAHAN, col_tiles(op));
+    return plan_bytes(1, 2) + problem_bytes(op, sk, m, basis_dtype == RTG_BF16, RTG_METHOD_GOLUB_KAHAN);
 }
 
 int rtg_gk_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t* v_offset, size_t* u_offset) {
@@ -1188,7 +1196,7 @@ int rtg_gk_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t
     if (rc) return rc;
     if ((rc = check_m(sk, m))) return rc;
     const int bf16 = basis_dtype == RTG_BF16;
-    const Layout L = problem_layout(op, sk, m, bf16, col_tiles(op));
+    const Layout L = problem_layout(op, sk, m, bf16, 0);
     const GKExtra E = gk_extra_layout(op, sk, m, bf16);
     if (v_offset) *v_offset = plan_bytes(1, 2) + L.V;
     if (u_offset) *u_offset = plan_bytes(1, 2) + L.total + E.V;

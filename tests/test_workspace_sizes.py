@@ -4,7 +4,8 @@ import os
 
 import pytest
 
-from paper_2603_00839_amd import rtg
+from paper_2603_00839_amd import rtg, synth
+import _util as U
 
 
 @pytest.fixture(scope="module")
@@ -28,3 +29,33 @@ def test_network_workspace_grows_with_the_image(lib, N):
         assert sizes[0] > 0 and sizes == sorted(sizes)
         sizes = [lib.rtg_cnn_workspace_bytes(N, other, n) for n in range(1, 300)]
         assert sizes[0] > 0 and sizes == sorted(sizes)
+
+
+# I1, I2, J, l1, l2, l3, m: the column tiles of a count of problems cross the
+# number up to which columns are cut in two
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(128, 128, 3, 64, 64, 3, 10), (128, 128, 1, 64, 64, 1, 10),
+                                   (128, 2048, 1, 128, 128, 1, 4), (72, 40, 3, 60, 40, 3, 4)], ids=str)
+@pytest.mark.parametrize("basis,method", [("F32", "METHOD_GMRES"), ("F32_BF16", "METHOD_GMRES"),
+                                          ("BF16", "METHOD_GMRES"), ("F32", "METHOD_GOLUB_KAHAN")])
+def test_batch_workspace_grows_with_the_batch(lib, shape, basis, method):
+    I1, I2, J, l1, l2, l3, m = shape
+    p = synth.small_problem(1, I1, I2, J, 2, 2, min(1, J - 1), l1, l2, l3, m)
+    op, sk = U.gpu_pair(p)
+    arr = (rtg.Problem * 140)()
+    for q in arr:
+        q.op, q.sk = op.handle, sk.handle
+        q.params = rtg.make_params(m, getattr(rtg, basis), delta=1.0, method=getattr(rtg, method))
+    sizes = [lib.rtg_batch_workspace_bytes(n, arr) for n in range(1, 141)]
+    assert sizes[0] > 0 and sizes == sorted(sizes)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("I1", [64, 72])
+def test_workspace_grows_with_the_image(lib, I1):
+    sizes = []
+    for I2 in range(1184, 1540, 16):          # 111 .. 144 column tiles
+        p = synth.small_problem(1, I1, I2, 3, 2, 2, 1, 60, 64, 3, 4)
+        op, sk = U.gpu_pair(p)
+        sizes.append((rtg.workspace_bytes(op, sk, 4), rtg.gk_workspace_bytes(op, sk, 4)))
+    assert sizes == sorted(sizes) and [b for _, b in sizes] == sorted(b for _, b in sizes)
