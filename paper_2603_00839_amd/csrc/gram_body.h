@@ -20,8 +20,7 @@
 //     then the breakdown test, the Givens update of the least-squares
 //     problem (11S) and the stopping decision.  It writes the coefficients
 //     for the next multi-AXPY (k_tile).
-// In the start mode it returns beta = ||S(R0)||; in the sketch-output mode it
-// writes the finished sketch in the column-major order of the C ABI.
+// In the start mode it returns beta = ||S(R0)||.
 //
 // Golub-Kahan mode (Sec. 4.5): the newest tensor X_c of one side (V_c, or
 // U_c on the side of Phi^T) was sketched with Omega and with the composed
@@ -319,7 +318,7 @@ struct GramSmem {
 // tensor once: the orthogonalisation traffic that a sketch avoids.
 template <bool FROB>
 __device__ __forceinline__ void gram_task(const Desc* __restrict__ descs, const int* __restrict__ starts,
-                                          int count, int mode, int j, float* sketch_out, int b, GramSmem& sm) {
+                                          int count, int mode, int j, int b, GramSmem& sm) {
     float* s_s = sm.s_s;
     float* s_v = sm.s_v;
     double* ds = sm.ds;
@@ -424,15 +423,6 @@ __device__ __forceinline__ void gram_task(const Desc* __restrict__ descs, const 
         __syncthreads();
     }
 
-    if (mode == GM_SKETCH_OUT) {
-        const int l1 = d.l1, l2 = d.l2;
-        for (int e = tid; e < E; e += 256) {
-            const int q = q0 + e / l3, c3 = e % l3;
-            const int a = q / l2, bb = q % l2;
-            sketch_out[(size_t)a + (size_t)l1 * (bb + (size_t)l2 * c3)] = s_s[e];
-        }
-        return;
-    }
     const size_t Lsz = (size_t)d.L;
     sv_dst = (mode == GM_STEP || mode == GM_GK) ? d.SV + (size_t)(j - 1) * Lsz + (size_t)q0 * l3 : nullptr;
     sv_n = E;

@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
                 tile_task<false, MB, false, 4, SBR>(descs, starts, a.count, k.mode, k.arg, k.arg, 0, k.b,
                                                *(TileShared<MB, false, 4, SBR>*)lds);
         } else {
-            gram_task<false>(descs, starts, a.count, k.mode, k.arg, nullptr, k.b, *(GramSmem*)lds);
+            gram_task<false>(descs, starts, a.count, k.mode, k.arg, k.b, *(GramSmem*)lds);
         }
         // every wave's stores are complete (in this XCD's L2) before the
         // barrier; then one write-back of the L2 (wave 0's release at agent

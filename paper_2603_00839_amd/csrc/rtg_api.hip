@@ -593,12 +593,12 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
         if (any_x0)
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_X0, 0, plan.rmax, plan.phi_jt, 0,
                                     s, plan.stencil, plan.phi_dma, plan.phi_toep));
-        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, nullptr, s, us));
+        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s, us));
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         for (int j = 1; j <= mmax; ++j) {
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                     plan.phi_jt, bf16, s, plan.stencil, plan.phi_dma, plan.phi_toep));
-            RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, nullptr, s, us));
+            RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, s, us));
             if (j < mmax || last_newv)
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
                                          plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
@@ -618,14 +618,14 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
                                     s, 1, plan.phi_dma, plan.phi_toep));
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0,
                                  plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
-        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, nullptr, s));
+        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s));
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         for (int j = 1; j <= mmax; ++j) {
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                     plan.phi_jt, bf16, s, 1, plan.phi_dma, plan.phi_toep));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_W, 0, 0, bf16, 0,
                                      plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
-            RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, nullptr, s));
+            RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, s));
             if (j < mmax || last_newv)
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
                                          plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
@@ -673,10 +673,10 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
         // in one pass (stored there too where X0 is absent, R0 = C); the
         // start step takes beta from S(V_1)
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV1, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
-        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, nullptr, s));
+        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s));
     } else {
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
-        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, nullptr, s));
+        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s));
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
     }
     for (int j = 1; j <= mmax; ++j) {
@@ -687,7 +687,7 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
         // there (the fused kernel's float32 variant runs at lower occupancy).
         // The same two kernels serve a bfloat16 basis whose vectors reach
         // 2^31 bytes (the fused kernel addresses them with 32-bit offsets).
-        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, nullptr, s));
+        RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, s));
         if (j < mmax || last_newv) {
             if (bf16 && plan.step_ok) {
                 RTG_TIMED(4, launch_step(dd, st, count, plan.total[KIND_TILE], j, plan.rmax, bf16, plan.l1max,
@@ -726,16 +726,16 @@ int run_gk(const Plan& plan, int count, int mmax, int bf16, bool any_x0, bool so
     if (any_x0) RTG_TIMED(0, launch_phi(dV, sp, count, tp, PS_X0, 0, plan.rmax, plan.phi_jt, 0, s, 0, plan.phi_dma, plan.phi_toep));
     // beta_1 = ||R0||_Theta, U_1 = R0 / beta_1 (with S(U_1) and S(Phi^T(U_1)))
     RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.block_rows));
-    RTG_TIMED(2, launch_gram(dU, sg, count, tg, GM_START, 0, nullptr, s));
+    RTG_TIMED(2, launch_gram(dU, sg, count, tg, GM_START, 0, s));
     RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.block_rows));
     for (int c = 1; c <= mmax; ++c) {
         // alpha_c; V_c = (Phi^T(U_c) - beta_c V_{c-1}) / alpha_c
-        RTG_TIMED(2, launch_gram(dU, sg, count, tg, GM_GK, c, nullptr, s));
+        RTG_TIMED(2, launch_gram(dU, sg, count, tg, GM_GK, c, s));
         RTG_TIMED(0, launch_phi(dU, sp, count, tp, PS_BASIS, c - 1, plan.rmax, plan.phi_jt, bf16, s, 0, plan.phi_dma, plan.phi_toep));
         RTG_TIMED(1, launch_tile(dV, st, count, tt, TM_GKNEW, c - 1, c - 1, bf16, 0, plan.l1max, s,
                                  c >= 2 ? c - 2 : 0, plan.tile_rows, 0, plan.block_rows));
         // beta_{c+1}, column c of B, Givens and stop test; U_{c+1} = (Phi(V_c) - alpha_c U_c) / beta_{c+1}
-        RTG_TIMED(2, launch_gram(dV, sg, count, tg, GM_GK, c, nullptr, s));
+        RTG_TIMED(2, launch_gram(dV, sg, count, tg, GM_GK, c, s));
         if (c < mmax || !solve) {   // the bidiagonalisation alone also forms U_{m+1}
             RTG_TIMED(0, launch_phi(dV, sp, count, tp, PS_BASIS, c - 1, plan.rmax, plan.phi_jt, bf16, s, 0, plan.phi_dma, plan.phi_toep));
             RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_GKNEW, c, c, bf16, 0, plan.l1max, s, c - 1, plan.tile_rows, 0, plan.block_rows));
@@ -1063,8 +1063,7 @@ int rtg_sketch(rtg_sk sk, int x_dtype, const void* X, float* SX, void* ws, size_
     RTG_HIP(launch_tile(plan.d_desc, starts_of(plan, KIND_TILE, 1), 1, plan.total[KIND_TILE], TM_SKETCH_SRC,
                         0, 0, x_dtype == RTG_BF16, x_dtype == RTG_BF16, plan.l1max, s, 0, plan.tile_rows, 0,
                         plan.block_rows));
-    RTG_HIP(launch_gram(plan.d_desc, starts_of(plan, KIND_GRAM, 1), 1, plan.total[KIND_GRAM], GM_SKETCH_OUT,
-                        0, SX, s));
+    RTG_HIP(launch_sketch_out(plan.d_desc, plan.total[KIND_GRAM], SX, s));
     return RTG_OK;
 }
 

@@ -500,7 +500,9 @@ hipError_t launch_tile(const Desc* d, const int* starts, int count, int total_ti
 hipError_t launch_step(const Desc* d, const int* starts, int count, int total_tiles, int j, int rmax,
                        int basis_bf16, int l1max, int toeplitz, hipStream_t s, int rows = 2);
 hipError_t launch_gram(const Desc* d, const int* starts, int count, int total_tiles,
-                       int mode, int j, float* sketch_out, hipStream_t s, int unsketched = 0);
+                       int mode, int j, hipStream_t s, int unsketched = 0);
+// the finished sketch of one tensor from its partials (one problem's descriptor)
+hipError_t launch_sketch_out(const Desc* d, int tiles, float* out, hipStream_t s);
 hipError_t launch_solve(const Desc* d, int count, int mmax, hipStream_t s);
 // sched (may be null): the persistent launch's words, zeroed by block 0
 hipError_t launch_init(const Desc* d, int count, hipStream_t s, int cycle = 0, int* sched = nullptr);
@@ -541,5 +543,5 @@ enum TileMode { TM_NEWV = 1, TM_ASSEMBLE = 2, TM_SKETCH_SRC = 3, TM_GKNEW = 4, T
 enum PhiSrc { PS_BASIS = 0, PS_X0 = 1, PS_X0_V1 = 2 };
 // k_gram modes
 // (GM_GK: one Golub-Kahan half-step, the sketched norm of the next tensor)
-enum GramMode { GM_START = 0, GM_STEP = 1, GM_SKETCH_OUT = 2, GM_GK = 3 };
+enum GramMode { GM_START = 0, GM_STEP = 1, GM_GK = 3 };
 }  // namespace rtg
