@@ -330,8 +330,9 @@ int rtg_solve_batched_fallback_end(int count, const rtg_problem* probs,
  *                 operators whose bands are all Toeplitz, phi_slab >= 1);
  *                 0: band rows streamed through LDS
  *   tile_rows     tile kernel: 16-row sketch tiles per wave, 2 (used where
- *                 the stacked sketch rows fit, else 4) or 4
- *   step_rows     fused bfloat16 Arnoldi step: the same, 2 or 4
+ *                 the stacked sketch rows fit, else 4, or 3 where a float32
+ *                 form needs no more) or 4
+ *   step_rows     fused bfloat16 Arnoldi step: 2 (else 4) or 4
  *   step_toeplitz fused step: 1 Toeplitz taps (all bands Toeplitz), 0 band rows
  *   gram_pairs    sketched inner products: (a, b) sketch pairs per workgroup:
  *                 256 (the library's own choice for the batch: 256, or fewer

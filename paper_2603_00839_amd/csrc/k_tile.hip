@@ -3,8 +3,13 @@
 
 namespace rtg {
 
+// float32 products: registers for two workgroups per compute unit.  Unbounded,
+// the form with four sketch tiles per wave took 296 registers and ran alone: 12
+// problems of 712x500x3 with 89 sketch rows (576 column tiles) 2.96 ms, 2.69
+// bounded, and 2.62 with three tiles per wave, which is enough for them; 32 of
+// 512x512x3 with 128 rows 5.84 -> 5.37 ms.  (The bfloat16 forms would spill.)
 template <bool BB, bool MB, bool SPLIT, int RPW, int SBR>
-__global__ void __launch_bounds__(256) k_tile(const Desc* __restrict__ descs,
+__global__ void __launch_bounds__(256, MB ? 1 : 2) k_tile(const Desc* __restrict__ descs,
                                               const int* __restrict__ starts, int count,
                                               int mode, int nterms_arg, int dst_index, int t0) {
     __shared__ TileShared<MB, SPLIT, RPW, SBR> sh;
@@ -13,7 +18,7 @@ __global__ void __launch_bounds__(256) k_tile(const Desc* __restrict__ descs,
 
 hipError_t launch_tile(const Desc* d, const int* starts, int count, int total_tiles, int mode,
                        int nterms, int dst_index, int basis_bf16, int src_bf16, int l1max, hipStream_t s,
-                       int first_term, int rows, int sketch_bf16, int block_rows) {
+                       int first_term, int rows, int sketch_bf16, int block_rows, int composed) {
 #define RTG_TILE_B(BBV, MBV, SPV, RPV, SBV)                                                       \
     hipLaunchKernelGGL((k_tile<BBV, MBV, SPV, RPV, SBV>), dim3(total_tiles), dim3(256), 0, s, d, starts, count, \
                        mode, nterms, dst_index, first_term)
@@ -23,7 +28,8 @@ hipError_t launch_tile(const Desc* d, const int* starts, int count, int total_ti
         else if (block_rows <= 128) RTG_TILE_B(BBV, MBV, SPV, RPV, 128);     \
         else RTG_TILE_B(BBV, MBV, SPV, RPV, 256);                            \
     } while (0)
-    const int rtiles = ((l1max + 15) / 16) * ((mode == TM_NEWV || mode == TM_GKNEW || mode == TM_NEWV1) ? 2 : 1);
+    const bool newv = mode == TM_NEWV || mode == TM_GKNEW || mode == TM_NEWV1;
+    const int rtiles = ((l1max + 15) / 16) * (newv && composed ? 2 : 1);
     const bool small = rtiles <= 8 && rows != 4;
     const bool split = (mode == TM_SKETCH_SRC || mode == TM_SKETCH_W) && !src_bf16;
     if (basis_bf16) {
@@ -35,7 +41,9 @@ hipError_t launch_tile(const Desc* d, const int* starts, int count, int total_ti
         if (split) { if (small) RTG_TILE(false, true, true, 2); else RTG_TILE(false, true, true, 4); }
         else { if (small) RTG_TILE(false, true, false, 2); else RTG_TILE(false, true, false, 4); }
     } else {
-        if (small) RTG_TILE(false, false, false, 2); else RTG_TILE(false, false, false, 4);
+        if (small) RTG_TILE(false, false, false, 2);
+        else if (rtiles <= 12 && rows != 4) RTG_TILE(false, false, false, 3);
+        else RTG_TILE(false, false, false, 4);
     }
 #undef RTG_TILE
 #undef RTG_TILE_B

@@ -348,7 +348,7 @@ struct Plan {
                        // 2 = also asynchronous (and at most three channels), 0 = single-word
     int phi_toep;      // operator: Toeplitz taps in registers
     int step_toep;     // fused step: Toeplitz taps
-    int tile_rows;     // sketch tiles per wave of the tile kernel (2 where they fit, or 4)
+    int tile_rows;     // sketch tiles per wave of the tile kernel (2: as few as fit, or 4)
     int step_rows;     // the same for the fused step
     int block_rows;    // rows per block of the tile kernel
     int skbf;          // sketch contractions on bfloat16 operands (every problem's descriptor says so)
@@ -407,23 +407,36 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
     // rows per block of the tile kernel: 256 reads whole kilobytes of a
     // column per wave and term (32 problems of 512x512x3, m = 50: 32.6 ms a
     // solve, 33.1 with 128 rows, 34.4 with 64), 64 or 128 where no column is
-    // longer; for the one-term passes of Golub-Kahan, where nothing is gained
-    // from a term's length, 64 where 256 would pad the columns by more than a
-    // twentieth (12 problems of 328x501x3: 6.33 against 6.71 ms; 20 of
-    // 512x512x3: 9.49 against 8.82)
-    int max_i1 = 0;
-    long long rows = 0, padded = 0;
+    // longer.
+    // The mixed form's tile is a third more registers: 128 keeps two workgroups
+    // per compute unit, or one where a sketch has more than 64 rows (31 problems
+    // of 480x313x3: 1.17 ms, with 256 rows 1.33).
+    // Blocks of 64 rows take so few registers that one workgroup more runs per
+    // compute unit.  The passes that read few terms (Golub-Kahan, general PSFs)
+    // and the mixed form take them where that saves a round of workgroups over
+    // the chip: 600 column tiles 0.89 to 0.99 of the time with 256 rows (mixed:
+    // 0.93 to 0.98 of 128), 780 tiles 1.01 to 1.10 (1.02 to 1.07), up to 510
+    // tiles 0.98 to 1.11.  float32 sketches of more than 64 rows have two
+    // workgroups per compute unit with any block: 256.
+    int max_i1 = 0, max_l1 = 0;
+    long long tiles = 0;
     for (auto& d : descs) {
         max_i1 = std::max(max_i1, d.I1);
-        rows += d.I1;
-        padded += (d.I1 + 255) / 256 * 256;
+        max_l1 = std::max(max_l1, d.l1);
+        tiles += d.ntile[KIND_TILE];
     }
+    tiles /= nsides;
+    const bool stencil = !descs.empty() && descs[0].st != nullptr;
+    const bool mixed = !descs.empty() && descs[0].skbf && !descs[0].bf16;
+    // (two 16-row sketch tiles per wave: as in launch_tile)
+    const bool low = (max_l1 + 15) / 16 * (stencil ? 1 : 2) <= 8 && !(tune && tune->tile_rows == 4);
+    auto rounds = [&](int per_cu) { return (tiles + 256 * per_cu - 1) / (256 * per_cu); };
     plan.block_rows = max_i1 <= 64 ? 64 : (max_i1 <= 128 ? 128 : 256);
-    if (nsides > 1 && 20 * (padded - rows) > rows) plan.block_rows = 64;
-    // (the mixed form's tile is a third more registers: 128 keeps two
-    // workgroups per compute unit.  31 problems of 480x313x3: 1.17 ms, with 256
-    // rows 1.33)
-    if (!descs.empty() && descs[0].skbf && !descs[0].bf16) plan.block_rows = std::min(plan.block_rows, 128);
+    if (mixed) {
+        plan.block_rows = std::min(plan.block_rows, low ? (rounds(3) < rounds(2) ? 64 : 128) : (rounds(2) < rounds(1) ? 64 : 128));
+    } else if ((nsides > 1 || stencil) && low && rounds(3) < rounds(2)) {
+        plan.block_rows = 64;
+    }
     plan.rmax = 1;
     for (int k = 0; k < NKIND; ++k) {
         int acc = 0;
@@ -619,7 +632,7 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0,
                                  plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows, 0));
         for (int j = 1; j <= mmax; ++j) {
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                     plan.phi_jt, bf16, s, 1, plan.phi_dma, plan.phi_toep));
@@ -628,7 +641,7 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
             RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, s));
             if (j < mmax || last_newv)
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
-                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows, 0));
         }
         if (solve) {
             RTG_TIMED(3, launch_solve(dd, count, mmax, s));

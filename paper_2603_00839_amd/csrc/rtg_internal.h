@@ -494,9 +494,11 @@ hipError_t launch_phi_single(int I1, int I2, int J, int r1, int r2, int rB, cons
 hipError_t launch_tile(const Desc* d, const int* starts, int count, int total_tiles,
                        int mode, int nterms, int dst_index, int basis_bf16, int src_bf16,
                        int l1max, hipStream_t s, int first_term = 0, int rows = 2, int sketch_bf16 = 0,
-                       int block_rows = 256);
+                       int block_rows = 256, int composed = 1);
 // rows (tile and step kernels): 16-row sketch tiles per wave, 2 where the
-// stacked sketch rows fit (the default), or 4
+// stacked sketch rows fit (the default; else 4, or 3 in the tile kernel's
+// float32 form where they fit), or 4.  composed: a new basis tensor is sketched
+// with the composed matrices too (not under a general PSF).
 hipError_t launch_step(const Desc* d, const int* starts, int count, int total_tiles, int j, int rmax,
                        int basis_bf16, int l1max, int toeplitz, hipStream_t s, int rows = 2);
 hipError_t launch_gram(const Desc* d, const int* starts, int count, int total_tiles,
