@@ -260,7 +260,15 @@ int rtg_solve(rtg_op op, rtg_sk sk, const float* C, const float* X0,
 /* Many independent problems (uneven sizes allowed) solved together: every
  * stage is one launch over the tiles of all problems.  probs is a HOST array.
  * One basis type, one method and one kind of operator (banded or general
- * PSF) per batch (RTG_E_ARG otherwise). */
+ * PSF) per batch (RTG_E_ARG otherwise).
+ * A batch gives the same bits every time, and no problem's result depends on
+ * another's data.  But how the sums over a tensor and over its sketch are
+ * split between workgroups follows the number and the sizes of the batch's
+ * problems, so the same problem alone, in another batch, or re-solved by the
+ * fallback beside other failures, may differ in rounding: by a few 1e-6 of
+ * ||X|| in float32 where one of the batches has at most 128 column tiles (J
+ * ceil(I2 / 32), summed over its problems) and the other more.
+ * The workspace of a batch holds every batch of some of its problems. */
 size_t rtg_batch_workspace_bytes(int count, const rtg_problem* probs);
 int rtg_solve_batched(int count, const rtg_problem* probs, void* ws,
                       size_t ws_bytes, void* stream);
@@ -401,7 +409,8 @@ int rtg_set_wait_limit(int polls);
  * layer w[co][t1][t2][ci] (t1, t2 in 0..2: offsets -1..+1 along i1 and i2)
  * followed by b[co].  Images are device arrays [N][3][I2][I1] (each the
  * column-major tensor layout above).  state is a caller-owned device buffer
- * of rtg_cnn_state_bytes(); ws of rtg_cnn_workspace_bytes(N, I1, I2). */
+ * of rtg_cnn_state_bytes(); ws of rtg_cnn_workspace_bytes(N, I1, I2), which
+ * grows with each of the three. */
 size_t rtg_cnn_state_bytes(void);
 size_t rtg_cnn_workspace_bytes(int N, int I1, int I2);
 /* copy the parameters in, zero the moments (synchronous on stream) */

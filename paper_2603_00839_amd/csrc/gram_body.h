@@ -535,6 +535,10 @@ __device__ __forceinline__ void gram_task(const Desc* __restrict__ descs, const 
     // else crosses workgroups here, so neither side needs a fence: a release
     // at agent scope writes back the whole L2 of the XCD, one workgroup after
     // the other (512 workgroups of 64 pairs took longer than 128 of 256).
+    // A workgroup's 1,568 bytes are no multiple of a cache line, so two XCDs may
+    // write parts of one line: the stores are written through by bytes, and the
+    // agent-scope loads do not take the copy of a line that this XCD's L2 may
+    // hold from its own stores or from an earlier step.
     __syncthreads();
     if (nwg > 1 && wave == 0) {
         double* dst = d.dots + (size_t)wgi * (MMAX + 2) * 2;

@@ -107,8 +107,8 @@ struct Desc {
     // workspace (device)
     void* V;            // (m+1) tensors
     float* W;           // Phi(V_j) / R0
-    float* PW;          // sketch partials of W: (J*n_i2t) x (l1*l2)
-    float* PV;          // sketch partials of the newest basis tensor
+    float* PW;          // sketch partials of W: (J*n_i2t*nrs) x (l1*l2)
+    float* PV;          // sketch partials of the newest basis tensor, as many
     float* SV;          // (m+1) x L sketched basis
     const float* SVx;   // Golub-Kahan: the other side's sketched basis
     double* dots;       // ntile[GRAM] x (m+2) x 2 partial inner products
