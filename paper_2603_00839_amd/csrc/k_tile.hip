@@ -3,13 +3,15 @@
 
 namespace rtg {
 
-// float32 products: registers for two workgroups per compute unit.  Unbounded,
-// the form with four sketch tiles per wave took 296 registers and ran alone: 12
-// problems of 712x500x3 with 89 sketch rows (576 column tiles) 2.96 ms, 2.69
-// bounded, and 2.62 with three tiles per wave, which is enough for them; 32 of
-// 512x512x3 with 128 rows 5.84 -> 5.37 ms.  (The bfloat16 forms would spill.)
+// Four float32 sketch tiles per wave take 296 registers with blocks of 256 rows:
+// one workgroup per compute unit.  Where three are enough (sketches of 65 to 96
+// rows) they are bounded to the registers of two: 12 problems of 712x500x3 with
+// 89 sketch rows (576 column tiles, m = 12) 2.96 -> 2.62 ms.  Four bounded to
+// the same spill a little, which costs 1 % where many terms are read (64 uneven
+// images, m = 40: 16.7 ms in this kernel, 16.9 bounded); the forms with two fit
+// by themselves, and the bound cost Golub-Kahan's 64-row blocks 1 %.
 template <bool BB, bool MB, bool SPLIT, int RPW, int SBR>
-__global__ void __launch_bounds__(256, MB ? 1 : 2) k_tile(const Desc* __restrict__ descs,
+__global__ void __launch_bounds__(256, RPW == 3 ? 2 : 1) k_tile(const Desc* __restrict__ descs,
                                               const int* __restrict__ starts, int count,
                                               int mode, int nterms_arg, int dst_index, int t0) {
     __shared__ TileShared<MB, SPLIT, RPW, SBR> sh;

@@ -416,8 +416,9 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
     // and the mixed form take them where that saves a round of workgroups over
     // the chip: 600 column tiles 0.89 to 0.99 of the time with 256 rows (mixed:
     // 0.93 to 0.98 of 128), 780 tiles 1.01 to 1.10 (1.02 to 1.07), up to 510
-    // tiles 0.98 to 1.11.  float32 sketches of more than 64 rows have two
-    // workgroups per compute unit with any block: 256.
+    // tiles 0.98 to 1.11.  With more than 96 sketch rows these passes take 128,
+    // the largest block of which two workgroups fit (Golub-Kahan, 24 problems of
+    // 456x501x3, sketch 128x128: 4.45 ms, 4.77 with 64 rows, 5.07 with 256).
     int max_i1 = 0, max_l1 = 0;
     long long tiles = 0;
     for (auto& d : descs) {
@@ -428,14 +429,16 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
     tiles /= nsides;
     const bool stencil = !descs.empty() && descs[0].st != nullptr;
     const bool mixed = !descs.empty() && descs[0].skbf && !descs[0].bf16;
-    // (two 16-row sketch tiles per wave: as in launch_tile)
-    const bool low = (max_l1 + 15) / 16 * (stencil ? 1 : 2) <= 8 && !(tune && tune->tile_rows == 4);
+    // 16-row sketch tiles per wave, as in launch_tile
+    const int stacked = (max_l1 + 15) / 16 * (stencil ? 1 : 2);
+    const int per_wave = (tune && tune->tile_rows == 4) || stacked > 12 ? 4 : (stacked > 8 ? 3 : 2);
+    const bool low = per_wave == 2;
     auto rounds = [&](int per_cu) { return (tiles + 256 * per_cu - 1) / (256 * per_cu); };
     plan.block_rows = max_i1 <= 64 ? 64 : (max_i1 <= 128 ? 128 : 256);
     if (mixed) {
         plan.block_rows = std::min(plan.block_rows, low ? (rounds(3) < rounds(2) ? 64 : 128) : (rounds(2) < rounds(1) ? 64 : 128));
-    } else if ((nsides > 1 || stencil) && low && rounds(3) < rounds(2)) {
-        plan.block_rows = 64;
+    } else if (nsides > 1 || stencil) {
+        plan.block_rows = std::min(plan.block_rows, low && rounds(3) < rounds(2) ? 64 : (per_wave == 4 ? 128 : 256));
     }
     plan.rmax = 1;
     for (int k = 0; k < NKIND; ++k) {
