@@ -9,9 +9,10 @@ namespace rtg {
 // 89 sketch rows (576 column tiles, m = 12) 2.96 -> 2.62 ms.  Four bounded to
 // the same spill a little, which costs 1 % where many terms are read (64 uneven
 // images, m = 40: 16.7 ms in this kernel, 16.9 bounded); the forms with two fit
-// by themselves, and the bound cost Golub-Kahan's 64-row blocks 1 %.
+// by themselves, and the bound cost Golub-Kahan's 64-row blocks 1 %.  The
+// two-plane form's 64-row blocks fit three workgroups only when bounded to them.
 template <bool BB, bool MB, bool SPLIT, int RPW, int SBR>
-__global__ void __launch_bounds__(256, RPW == 3 ? 2 : 1) k_tile(const Desc* __restrict__ descs,
+__global__ void __launch_bounds__(256, RPW == 3 ? 2 : (SPLIT && RPW == 2 && SBR == 64 ? 3 : 1)) k_tile(const Desc* __restrict__ descs,
                                               const int* __restrict__ starts, int count,
                                               int mode, int nterms_arg, int dst_index, int t0) {
     __shared__ TileShared<MB, SPLIT, RPW, SBR> sh;

@@ -408,17 +408,18 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
     // column per wave and term (32 problems of 512x512x3, m = 50: 32.6 ms a
     // solve, 33.1 with 128 rows, 34.4 with 64), 64 or 128 where no column is
     // longer.
-    // The mixed form's tile is a third more registers: 128 keeps two workgroups
-    // per compute unit, or one where a sketch has more than 64 rows (31 problems
+    // The mixed form's tile is a third more registers: at most 128 (31 problems
     // of 480x313x3: 1.17 ms, with 256 rows 1.33).
-    // Blocks of 64 rows take so few registers that one workgroup more runs per
-    // compute unit.  The passes that read few terms (Golub-Kahan, general PSFs)
-    // and the mixed form take them where that saves a round of workgroups over
-    // the chip: 600 column tiles 0.89 to 0.99 of the time with 256 rows (mixed:
-    // 0.93 to 0.98 of 128), 780 tiles 1.01 to 1.10 (1.02 to 1.07), up to 510
-    // tiles 0.98 to 1.11.  With more than 96 sketch rows these passes take 128,
-    // the largest block of which two workgroups fit (Golub-Kahan, 24 problems of
-    // 456x501x3, sketch 128x128: 4.45 ms, 4.77 with 64 rows, 5.07 with 256).
+    // Blocks of 64 rows leave registers for one workgroup more per compute unit,
+    // but for float32 sketches of more than 64 rows.  The mixed form and the
+    // passes that read few terms (Golub-Kahan, general PSFs) take them where
+    // that saves a round of workgroups over the chip: at 600 column tiles 0.89 to
+    // 0.99 of the time with 256 rows (mixed: 0.93 to 0.98 of 128), at 780 1.01 to
+    // 1.10 (1.02 to 1.07), up to 510 0.98 to 1.11; mixed sketches of more than 64
+    // rows 0.84 to 0.96 of 128 from 270 tiles on, 1.01 to 1.10 up to 180.  Short
+    // float32 passes with more than 96 sketch rows take 128, the largest of which
+    // two workgroups fit (Golub-Kahan, 24 problems of 456x501x3, sketch 128x128:
+    // 4.45 ms, 4.77 with 64 rows, 5.07 with 256).
     int max_i1 = 0, max_l1 = 0;
     long long tiles = 0;
     for (auto& d : descs) {
@@ -427,18 +428,18 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
         tiles += d.ntile[KIND_TILE];
     }
     tiles /= nsides;
-    const bool stencil = !descs.empty() && descs[0].st != nullptr;
-    const bool mixed = !descs.empty() && descs[0].skbf && !descs[0].bf16;
-    // 16-row sketch tiles per wave, as in launch_tile
-    const int stacked = (max_l1 + 15) / 16 * (stencil ? 1 : 2);
-    const int per_wave = (tune && tune->tile_rows == 4) || stacked > 12 ? 4 : (stacked > 8 ? 3 : 2);
-    const bool low = per_wave == 2;
-    auto rounds = [&](int per_cu) { return (tiles + 256 * per_cu - 1) / (256 * per_cu); };
     plan.block_rows = max_i1 <= 64 ? 64 : (max_i1 <= 128 ? 128 : 256);
-    if (mixed) {
-        plan.block_rows = std::min(plan.block_rows, low ? (rounds(3) < rounds(2) ? 64 : 128) : (rounds(2) < rounds(1) ? 64 : 128));
-    } else if (nsides > 1 || stencil) {
-        plan.block_rows = std::min(plan.block_rows, low && rounds(3) < rounds(2) ? 64 : (per_wave == 4 ? 128 : 256));
+    const bool stencil = !descs.empty() && descs[0].st != nullptr;
+    const bool skbf = !descs.empty() && descs[0].skbf, mixed = skbf && !descs[0].bf16;
+    if (mixed || nsides > 1 || stencil) {
+        // 16-row sketch tiles per wave, as in launch_tile, and workgroups per
+        // compute unit with blocks of 64 rows and of `wide`
+        const int stacked = (max_l1 + 15) / 16 * (stencil ? 1 : 2);
+        const int per_wave = (tune && tune->tile_rows == 4) || stacked > (skbf ? 8 : 12) ? 4 : (stacked > 8 ? 3 : 2);
+        const int wide = mixed || (per_wave == 4 && !skbf) ? 128 : 256;
+        const int wgs64 = per_wave == 2 ? 3 : 2, wgs_wide = per_wave == 4 && skbf ? 1 : 2;
+        auto rounds = [&](int wgs) { return (tiles + 256 * wgs - 1) / (256 * wgs); };
+        plan.block_rows = std::min(plan.block_rows, rounds(wgs64) < rounds(wgs_wide) ? 64 : wide);
     }
     plan.rmax = 1;
     for (int k = 0; k < NKIND; ++k) {

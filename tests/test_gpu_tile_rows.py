@@ -21,13 +21,14 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("I1", [136, 264])
-@pytest.mark.parametrize("form", ["golub_kahan", "psf", "mixed", "mixed_wide", "f32"])
+@pytest.mark.parametrize("form", ["golub_kahan", "golub_kahan_bf16", "golub_kahan_bf16_wide", "psf", "psf_mixed", "mixed",
+                                  "mixed_wide", "f32"])
 def test_rows_per_block_leave_the_bits(form, I1):
     import torch
     from paper_2603_00839_amd import rtg
-    I2, J, l1, l2, m = 232, 3, 72 if form == "mixed_wide" else 16, 16, 5     # 24 column tiles
+    I2, J, l1, l2, m = 232, 3, 72 if form.endswith("wide") else 16, 16, 5     # 24 column tiles
     rng = np.random.default_rng(I1)
-    if form == "psf":
+    if form.startswith("psf"):
         p = synth.psf_problem(9, I1, I2, J, r=3, l1=l1, l2=l2, m=m)
         op = rtg.setup_operator_psf(I1, I2, J, p.psf, p.b_band)
         sk = rtg.setup_sketch(I1, I2, J, p.om1, p.om2, p.om3)
@@ -35,8 +36,8 @@ def test_rows_per_block_leave_the_bits(form, I1):
         p = synth.small_problem(9, I1, I2, J, 3, 3, 1, l1, l2, J, m)
         op, sk = U.gpu_pair(p)
     Cs = [U.to_dev(rng.standard_normal((I1, I2, J))) for _ in range(26)]
-    basis = rtg.F32_BF16 if form.startswith("mixed") else rtg.F32
-    method = rtg.METHOD_GOLUB_KAHAN if form == "golub_kahan" else rtg.METHOD_GMRES
+    basis = rtg.F32_BF16 if "mixed" in form else (rtg.BF16 if "bf16" in form else rtg.F32)
+    method = rtg.METHOD_GOLUB_KAHAN if form.startswith("golub_kahan") else rtg.METHOD_GMRES
 
     def solve(n):
         plan = rtg.BatchPlan([op] * n, [sk] * n, Cs[:n], [None] * n,
