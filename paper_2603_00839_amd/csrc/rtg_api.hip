@@ -350,7 +350,10 @@ struct Plan {
     int step_toep;     // fused step: Toeplitz taps
     int tile_rows;     // sketch tiles per wave of the tile kernel (2: as few as fit, or 4)
     int step_rows;     // the same for the fused step
-    int block_rows;    // rows per block of the tile kernel
+    int block_rows;    // rows per block of the tile kernel,
+    int short_rows;    // and of its passes over fewer than short_terms terms
+    int short_terms;
+    int rows_for(int nterms) const { return nterms < short_terms ? short_rows : block_rows; }
     int skbf;          // sketch contractions on bfloat16 operands (every problem's descriptor says so)
     Desc* d_desc_r;    // restart cycles: the descriptors with X0 = X (null without restarts)
     int persist;       // the Arnoldi process as one persistent launch
@@ -410,16 +413,6 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
     // longer.
     // The mixed form's tile is a third more registers: at most 128 (31 problems
     // of 480x313x3: 1.17 ms, with 256 rows 1.33).
-    // Blocks of 64 rows leave registers for one workgroup more per compute unit,
-    // but for float32 sketches of more than 64 rows.  The mixed form and the
-    // passes that read few terms (Golub-Kahan, general PSFs) take them where
-    // that saves a round of workgroups over the chip: at 600 column tiles 0.89 to
-    // 0.99 of the time with 256 rows (mixed: 0.93 to 0.98 of 128), at 780 1.01 to
-    // 1.10 (1.02 to 1.07), up to 510 0.98 to 1.11; mixed sketches of more than 64
-    // rows 0.84 to 0.96 of 128 from 270 tiles on, 1.01 to 1.10 up to 180.  Short
-    // float32 passes with more than 96 sketch rows take 128, the largest of which
-    // two workgroups fit (Golub-Kahan, 24 problems of 456x501x3, sketch 128x128:
-    // 4.45 ms, 4.77 with 64 rows, 5.07 with 256).
     int max_i1 = 0, max_l1 = 0;
     long long tiles = 0;
     for (auto& d : descs) {
@@ -428,18 +421,35 @@ int build_plan(std::vector<Desc>& descs, void* ws, hipStream_t s, Plan& plan, in
         tiles += d.ntile[KIND_TILE];
     }
     tiles /= nsides;
-    plan.block_rows = max_i1 <= 64 ? 64 : (max_i1 <= 128 ? 128 : 256);
     const bool stencil = !descs.empty() && descs[0].st != nullptr;
     const bool skbf = !descs.empty() && descs[0].skbf, mixed = skbf && !descs[0].bf16;
+    const int longest = max_i1 <= 64 ? 64 : (max_i1 <= 128 ? 128 : 256);
+    plan.block_rows = plan.short_rows = std::min(longest, mixed ? 128 : 256);
+    plan.short_terms = 0;
+    // Blocks of 64 rows leave registers for one workgroup more per compute unit,
+    // but for float32 sketches of more than 64 rows.  The mixed form,
+    // Golub-Kahan and general PSFs take them in passes that read few terms, where
+    // that saves a round of workgroups over the chip: Golub-Kahan (one term) at
+    // 600 column tiles 0.89 to 0.94 of the time with 256 rows, at 780 1.01 to
+    // 1.07, up to 510 0.98 to 1.10.  The more terms, the more the longer reads of
+    // a column count: solves at 600 tiles (general PSF; mixed) take 0.96 to 0.98
+    // (0.95 to 0.99) of the time with 64 rows throughout at m = 12, 1.00 to 1.02
+    // (0.98 to 1.02) at m = 25 and 1.04 to 1.09 (1.00 to 1.06) at m = 50, so the
+    // line lies at 8 terms.  Mixed sketches of more than 64 rows, one
+    // workgroup against two, gain for twice as long: 0.92 to 0.97, 0.97 to 0.98
+    // and 1.00 to 1.05.  Short float32 passes with more than 96 sketch rows take
+    // 128, the largest of which two workgroups fit (Golub-Kahan, 24 problems of
+    // 456x501x3, sketch 128x128: 4.45 ms, 4.77 with 64 rows, 5.07 with 256).
     if (mixed || nsides > 1 || stencil) {
         // 16-row sketch tiles per wave, as in launch_tile, and workgroups per
-        // compute unit with blocks of 64 rows and of `wide`
+        // compute unit with 64 rows and with more
         const int stacked = (max_l1 + 15) / 16 * (stencil ? 1 : 2);
         const int per_wave = (tune && tune->tile_rows == 4) || stacked > (skbf ? 8 : 12) ? 4 : (stacked > 8 ? 3 : 2);
-        const int wide = mixed || (per_wave == 4 && !skbf) ? 128 : 256;
-        const int wgs64 = per_wave == 2 ? 3 : 2, wgs_wide = per_wave == 4 && skbf ? 1 : 2;
-        auto rounds = [&](int wgs) { return (tiles + 256 * wgs - 1) / (256 * wgs); };
-        plan.block_rows = std::min(plan.block_rows, rounds(wgs64) < rounds(wgs_wide) ? 64 : wide);
+        const int wgs64 = per_wave == 2 ? 3 : 2, wgs = per_wave == 4 && skbf ? 1 : 2;
+        auto rounds = [&](int w) { return (tiles + 256 * w - 1) / (256 * w); };
+        if (rounds(wgs64) < rounds(wgs)) plan.short_rows = 64;
+        else if (per_wave == 4 && !skbf) plan.short_rows = std::min(longest, 128);
+        plan.short_terms = per_wave == 4 ? 16 : 8;
     }
     plan.rmax = 1;
     for (int k = 0; k < NKIND; ++k) {
@@ -611,19 +621,19 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_X0, 0, plan.rmax, plan.phi_jt, 0,
                                     s, plan.stencil, plan.phi_dma, plan.phi_toep));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s, us));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(0)));
         for (int j = 1; j <= mmax; ++j) {
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                     plan.phi_jt, bf16, s, plan.stencil, plan.phi_dma, plan.phi_toep));
             RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, s, us));
             if (j < mmax || last_newv)
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
-                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(j)));
         }
         if (solve) {
             RTG_TIMED(3, launch_solve(dd, count, mmax, s));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0,
-                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(mmax)));
         }
         return RTG_OK;
     }
@@ -634,23 +644,23 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_X0, 0, plan.rmax, plan.phi_jt, 0,
                                     s, 1, plan.phi_dma, plan.phi_toep));
         RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0,
-                                 plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+                                 plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(0)));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows, 0));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(0), 0));
         for (int j = 1; j <= mmax; ++j) {
             RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                     plan.phi_jt, bf16, s, 1, plan.phi_dma, plan.phi_toep));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_W, 0, 0, bf16, 0,
-                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(0)));
             RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_STEP, j, s));
             if (j < mmax || last_newv)
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
-                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows, 0));
+                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(j), 0));
         }
         if (solve) {
             RTG_TIMED(3, launch_solve(dd, count, mmax, s));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0,
-                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+                                     plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(mmax)));
         }
         return RTG_OK;
     }
@@ -677,7 +687,7 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
         if (solve) {
             RTG_TIMED(3, launch_solve(dd, count, mmax, s));
             RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0,
-                                     plan.tile_rows, plan.skbf, plan.block_rows));
+                                     plan.tile_rows, plan.skbf, plan.rows_for(mmax)));
         }
         return RTG_OK;
     }
@@ -689,12 +699,12 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
         // V_1 = R0 (scale 1, set by the init kernel) with both its sketches
         // in one pass (stored there too where X0 is absent, R0 = C); the
         // start step takes beta from S(V_1)
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV1, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV1, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(0)));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s));
     } else {
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(0)));
         RTG_TIMED(2, launch_gram(dd, sg, count, plan.total[KIND_GRAM], GM_START, cycle, s));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(0)));
     }
     for (int j = 1; j <= mmax; ++j) {
         // S(V_j) and S(Phi(V_j)) come from the pass that formed V_j.  With a
@@ -713,13 +723,13 @@ int run_solver(const Plan& plan, int count, int mmax, int bf16, bool any_x0, boo
                 RTG_TIMED(0, launch_phi(dd, sp, count, plan.total[KIND_PHI], PS_BASIS, j - 1, plan.rmax,
                                         plan.phi_jt, bf16, s, 0, plan.phi_dma, plan.phi_toep));
                 RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_NEWV, j, j, bf16, 0,
-                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+                                         plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(j)));
             }
         }
     }
     if (solve) {
         RTG_TIMED(3, launch_solve(dd, count, mmax, s));
-        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.block_rows));
+        RTG_TIMED(1, launch_tile(dd, st, count, plan.total[KIND_TILE], TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, plan.skbf, plan.rows_for(mmax)));
     }
     return RTG_OK;
 }
@@ -742,25 +752,25 @@ int run_gk(const Plan& plan, int count, int mmax, int bf16, bool any_x0, bool so
     RTG_HIP(launch_compose(plan.d_desc, 2 * count, plan.compose_max, s));
     if (any_x0) RTG_TIMED(0, launch_phi(dV, sp, count, tp, PS_X0, 0, plan.rmax, plan.phi_jt, 0, s, 0, plan.phi_dma, plan.phi_toep));
     // beta_1 = ||R0||_Theta, U_1 = R0 / beta_1 (with S(U_1) and S(Phi^T(U_1)))
-    RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.block_rows));
+    RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_SKETCH_SRC, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.rows_for(0)));
     RTG_TIMED(2, launch_gram(dU, sg, count, tg, GM_START, 0, s));
-    RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.block_rows));
+    RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_NEWV, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.rows_for(0)));
     for (int c = 1; c <= mmax; ++c) {
         // alpha_c; V_c = (Phi^T(U_c) - beta_c V_{c-1}) / alpha_c
         RTG_TIMED(2, launch_gram(dU, sg, count, tg, GM_GK, c, s));
         RTG_TIMED(0, launch_phi(dU, sp, count, tp, PS_BASIS, c - 1, plan.rmax, plan.phi_jt, bf16, s, 0, plan.phi_dma, plan.phi_toep));
         RTG_TIMED(1, launch_tile(dV, st, count, tt, TM_GKNEW, c - 1, c - 1, bf16, 0, plan.l1max, s,
-                                 c >= 2 ? c - 2 : 0, plan.tile_rows, 0, plan.block_rows));
+                                 c >= 2 ? c - 2 : 0, plan.tile_rows, 0, plan.rows_for(1)));
         // beta_{c+1}, column c of B, Givens and stop test; U_{c+1} = (Phi(V_c) - alpha_c U_c) / beta_{c+1}
         RTG_TIMED(2, launch_gram(dV, sg, count, tg, GM_GK, c, s));
         if (c < mmax || !solve) {   // the bidiagonalisation alone also forms U_{m+1}
             RTG_TIMED(0, launch_phi(dV, sp, count, tp, PS_BASIS, c - 1, plan.rmax, plan.phi_jt, bf16, s, 0, plan.phi_dma, plan.phi_toep));
-            RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_GKNEW, c, c, bf16, 0, plan.l1max, s, c - 1, plan.tile_rows, 0, plan.block_rows));
+            RTG_TIMED(1, launch_tile(dU, st, count, tt, TM_GKNEW, c, c, bf16, 0, plan.l1max, s, c - 1, plan.tile_rows, 0, plan.rows_for(1)));
         }
     }
     if (solve) {
         RTG_TIMED(3, launch_solve(dV, count, mmax, s));
-        RTG_TIMED(1, launch_tile(dV, st, count, tt, TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.block_rows));
+        RTG_TIMED(1, launch_tile(dV, st, count, tt, TM_ASSEMBLE, 0, 0, bf16, 0, plan.l1max, s, 0, plan.tile_rows, 0, plan.rows_for(mmax)));
     }
     return RTG_OK;
 }
@@ -1079,7 +1089,7 @@ int rtg_sketch(rtg_sk sk, int x_dtype, const void* X, float* SX, void* ws, size_
     if (rc) return rc;
     RTG_HIP(launch_tile(plan.d_desc, starts_of(plan, KIND_TILE, 1), 1, plan.total[KIND_TILE], TM_SKETCH_SRC,
                         0, 0, x_dtype == RTG_BF16, x_dtype == RTG_BF16, plan.l1max, s, 0, plan.tile_rows, 0,
-                        plan.block_rows));
+                        plan.rows_for(0)));
     RTG_HIP(launch_sketch_out(plan.d_desc, plan.total[KIND_GRAM], SX, s));
     return RTG_OK;
 }

@@ -1,6 +1,6 @@
-"""Which form of the tile kernel a batch takes: 64 rows per block where that
-saves a round of workgroups over the chip (513 to 768 column tiles), and two,
-three or four sketch tiles of 16 rows per wave.
+"""Which form of the tile kernel a batch takes: in passes over few terms 64 rows
+per block where that saves a round of workgroups over the chip (513 to 768
+column tiles), and two, three or four sketch tiles of 16 rows per wave.
 
 Rows per block only cut the loop over a column: the same problem in batches on
 both sides of the rule has to give the same bits.  Sketch tiles per wave:
@@ -26,7 +26,7 @@ pytestmark = pytest.mark.gpu
 def test_rows_per_block_leave_the_bits(form, I1):
     import torch
     from paper_2603_00839_amd import rtg
-    I2, J, l1, l2, m = 232, 3, 72 if form.endswith("wide") else 16, 16, 5     # 24 column tiles
+    I2, J, l1, l2, m = 232, 3, 72 if form.endswith("wide") else 16, 16, 10    # 24 column tiles; steps on both sides of 8 terms
     rng = np.random.default_rng(I1)
     if form.startswith("psf"):
         p = synth.psf_problem(9, I1, I2, J, r=3, l1=l1, l2=l2, m=m)
