@@ -90,15 +90,22 @@ int part_rows(const rtg_op_s* op, long long total) {
 }
 int whole_rows(const rtg_op_s* op) { return (op->I1 + 63) / 64 * 64; }
 
-// Partial sketches that a problem's workspace holds: those of the halves where
-// any batch with this problem would take them, and no fewer for a problem with
-// more column tiles, so that the size depends on the problem alone and grows
-// with it (a workspace of the largest batch holds every smaller one).
-long long max_parts(const rtg_op_s* op, int bf16) {
-    const long long tiles = col_tiles(op);
-    if (bf16 || op->I1 <= 64) return tiles;
-    return std::max(tiles, 2 * std::min(tiles, PART_TILES));
-}
+// Room beyond whole columns for the halves' partial sketches (PW and PV of
+// problem_layout).  Only batches of at most PART_TILES column tiles take halves,
+// so a larger one keeps room for as much as any of its smaller parts would need:
+// the size of a workspace grows with the batch and with every problem of it, and
+// a workspace made for the largest call holds the smaller ones.
+struct PartRoom {
+    size_t sum = 0, widest = 0;
+    void add(const rtg_op_s* op, const rtg_sk_s* sk, int bf16) {
+        if (bf16 || sk->identity || op->I1 <= 64) return;
+        const size_t tile = (size_t)sk->l1 * sk->l2 * sizeof(float);
+        sum += 2 * align_up(col_tiles(op) * tile);
+        widest = std::max(widest, tile);
+    }
+    // (at most PART_TILES problems in a batch of as many tiles, each rounded up)
+    size_t bytes() const { return std::min(sum, 2 * (size_t)PART_TILES * (widest + 256)); }
+};
 
 // total: column tiles of the whole batch (0: whole columns)
 Layout problem_layout(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, long long total) {
@@ -115,7 +122,7 @@ Layout problem_layout(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, l
     L.ntile_phi = phi_tiles(op->I1, op->I2, op->J, phi_jt(op->J));
     // an identity sketch keeps no partials, stored sketches or composed matrices
     const bool sk_bufs = !sk->identity;
-    const size_t part = sk_bufs ? (size_t)max_parts(op, bf16) * sk->l1 * sk->l2 * sizeof(float) : 0;
+    const size_t part = sk_bufs ? (size_t)L.ntile_tile * sk->l1 * sk->l2 * sizeof(float) : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) { off = align_up(off); size_t at = off; off += bytes; return at; };
     L.V = take((size_t)(m + 1) * n * es);
@@ -191,6 +198,7 @@ void fill_gk_sides(Desc& d, Desc& u, const rtg_op_s* op, const rtg_sk_s* sk, int
     u.SVx = d.SV;
 }
 
+// (with whole columns: PartRoom has the rest)
 size_t problem_bytes(const rtg_op_s* op, const rtg_sk_s* sk, int m, int bf16, int method) {
     size_t b = problem_layout(op, sk, m, bf16, 0).total;
     if (method == RTG_METHOD_GOLUB_KAHAN) b += gk_extra_layout(op, sk, m, bf16).total;
@@ -1156,14 +1164,16 @@ int rtg_sketch_noalloc(rtg_sk sk, int x_dtype, const void* X, float* SX, void* s
 size_t rtg_workspace_bytes(rtg_op op, rtg_sk sk, int m, int basis_dtype) {
     if (check_pair(op, sk) || check_m(sk, m)) return 0;
     // (room for the restart-cycle descriptor copy of rtg_solve with restarts)
-    return plan_bytes(1, 1, true) + problem_layout(op, sk, m, basis_dtype == RTG_BF16, 0).total;
+    PartRoom room;
+    room.add(op, sk, basis_dtype == RTG_BF16);
+    return plan_bytes(1, 1, true) + problem_layout(op, sk, m, basis_dtype == RTG_BF16, 0).total + room.bytes();
 }
 
 int rtg_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t* v_offset, size_t* sv_offset) {
     int rc = check_pair(op, sk);
     if (rc) return rc;
     if ((rc = check_m(sk, m))) return rc;
-    Layout L = problem_layout(op, sk, m, basis_dtype == RTG_BF16, 0);
+    Layout L = problem_layout(op, sk, m, basis_dtype == RTG_BF16, col_tiles(op));
     if (v_offset) *v_offset = plan_bytes(1) + L.V;
     if (sv_offset) *sv_offset = plan_bytes(1) + L.SV;
     return RTG_OK;
@@ -1203,18 +1213,22 @@ size_t rtg_batch_workspace_bytes(int count, const rtg_problem* probs) {
     bool restart = false;
     for (int p = 0; p < count; ++p) restart = restart || probs[p].params.restarts > 0;
     size_t total = plan_bytes(count, method == RTG_METHOD_GOLUB_KAHAN ? 2 : 1, restart);
+    PartRoom room;
     for (int p = 0; p < count; ++p) {
         const rtg_problem& q = probs[p];
         if (check_pair(q.op, q.sk) || check_m(q.sk, q.params.m)) return 0;
         if (q.params.method != method) return 0;
         total += problem_bytes(q.op, q.sk, q.params.m, q.params.basis_dtype == RTG_BF16, method);
+        room.add(q.op, q.sk, q.params.basis_dtype == RTG_BF16);
     }
-    return total;
+    return total + room.bytes();
 }
 
 size_t rtg_gk_workspace_bytes(rtg_op op, rtg_sk sk, int m, int basis_dtype) {
     if (check_pair(op, sk) || check_m(sk, m)) return 0;
-    return plan_bytes(1, 2) + problem_bytes(op, sk, m, basis_dtype == RTG_BF16, RTG_METHOD_GOLUB_KAHAN);
+    PartRoom room;
+    room.add(op, sk, basis_dtype == RTG_BF16);
+    return plan_bytes(1, 2) + problem_bytes(op, sk, m, basis_dtype == RTG_BF16, RTG_METHOD_GOLUB_KAHAN) + room.bytes();
 }
 
 int rtg_gk_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t* v_offset, size_t* u_offset) {
@@ -1222,7 +1236,7 @@ int rtg_gk_workspace_layout(rtg_op op, rtg_sk sk, int m, int basis_dtype, size_t
     if (rc) return rc;
     if ((rc = check_m(sk, m))) return rc;
     const int bf16 = basis_dtype == RTG_BF16;
-    const Layout L = problem_layout(op, sk, m, bf16, 0);
+    const Layout L = problem_layout(op, sk, m, bf16, col_tiles(op));
     const GKExtra E = gk_extra_layout(op, sk, m, bf16);
     if (v_offset) *v_offset = plan_bytes(1, 2) + L.V;
     if (u_offset) *u_offset = plan_bytes(1, 2) + L.total + E.V;

@@ -2,6 +2,7 @@
 call holds every smaller one."""
 import os
 
+import numpy as np
 import pytest
 
 from paper_2603_00839_amd import rtg, synth
@@ -59,3 +60,34 @@ def test_workspace_grows_with_the_image(lib, I1):
         op, sk = U.gpu_pair(p)
         sizes.append((rtg.workspace_bytes(op, sk, 4), rtg.gk_workspace_bytes(op, sk, 4)))
     assert sizes == sorted(sizes) and [b for _, b in sizes] == sorted(b for _, b in sizes)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("method", ["METHOD_GMRES", "METHOD_GOLUB_KAHAN"])
+def test_workspace_of_a_batch_holds_its_parts(method):
+    """The workspace of 70 problems (210 column tiles, whole columns), filled
+    with NaN, for the first 70, 42 (126, halves), 43 and 1 of them: the bits of
+    a plan with its own workspace, and not a byte written past the size asked for."""
+    import torch
+    I1, I2, J, l1, l2, l3, m = 72, 40, 3, 60, 40, 3, 4
+    p = synth.small_problem(1, I1, I2, J, 2, 2, 1, l1, l2, l3, m)
+    op, sk = U.gpu_pair(p)
+    rng = np.random.default_rng(2)
+    Cs = [U.to_dev(rng.standard_normal((I1, I2, J))) for _ in range(70)]
+    prm = rtg.make_params(m, rtg.F32, mu=1e-2, method=getattr(rtg, method))
+
+    def plan(n):
+        return rtg.BatchPlan([op] * n, [sk] * n, Cs[:n], [None] * n, [prm] * n)
+
+    whole = plan(70).ws
+    for n in (70, 42, 43, 1):
+        own = plan(n)
+        want = [x.clone() for x in own.run()]
+        size = own.ws.numel()
+        assert size <= whole.numel()
+        whole.fill_(255)
+        other = plan(n)
+        other.ws = whole
+        got = other.run()
+        assert all(torch.equal(a, b) for a, b in zip(want, got)), n
+        assert bool((whole[size:] == 255).all()), n
